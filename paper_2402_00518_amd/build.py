@@ -17,7 +17,8 @@ CSRC = os.path.join(PKG, "csrc")
 BUILD = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libeetune.so")
 
-SOURCES = ["kernels.hip", "optim.hip", "decode.hip", "ee_abi.cpp"]
+SOURCES = ["gemm_weight_grad.hip", "gemm_logits.hip", "gemm_mlp_forward.hip", "gemm_mlp_backward.hip",
+           "kernels.hip", "optim.hip", "decode.hip", "ee_abi.cpp"]
 ARCH = "gfx950"
 
 HIPCC_FLAGS = [

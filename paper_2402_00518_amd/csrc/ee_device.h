@@ -94,4 +94,16 @@ __device__ __forceinline__ float warp_max(float v) {
   return v;
 }
 
+// Runs a launcher's body with T the element type.
+#define EE_DISPATCH(f32, ...)            \
+  do {                                   \
+    if (f32) {                           \
+      using T = float;                   \
+      __VA_ARGS__;                       \
+    } else {                             \
+      using T = bf16_t;                  \
+      __VA_ARGS__;                       \
+    }                                    \
+  } while (0)
+
 }  // namespace ee

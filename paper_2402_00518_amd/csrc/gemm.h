@@ -7,23 +7,21 @@
 // contiguous).  K-major tiles sit in LDS as rows of K; bf16 MN-major tiles
 // are copied as they are (k-rows) and transposed by the fragment reads
 // themselves (ds_read_b64_tr_b16), so neither side spends ALU work on the
-// layout.  (fp32 MN-major operands, used only by the fp32 path, are
-// transposed in registers on their way into LDS.)
+// layout.  (fp32 MN-major operands are transposed in registers on their way
+// into LDS.)
 //
-// A tile configuration fixes the output tile (BM x BN) and the part of it
-// each wave64 owns (WM x WN = MB x NB blocks of 32 x 32 accumulators).  Each
-// LDS tile row holds 128 bytes of K (64 bf16 or 32 fp32 values),
-// XOR-swizzled in 16-byte chunks so that fragment reads are free of bank
-// conflicts (see lds_off).  Two LDS stages; the next stage's global loads are in
-// flight (in registers) while the current stage feeds the matrix cores.
+// bf16 products (gemm_block_b16) run a 256 x 256 tile on 8 wave64 waves of
+// 128 x 64, v_mfma_f32_16x16x32_bf16: operand tiles go from memory straight
+// into LDS (global_load_lds_dwordx4, two stages of 64 values of K) and the
+// two waves of a SIMD take turns, one in its MFMAs while the other reads its
+// fragments.  fp32 products (gemm_block) run a 128 x 128 tile on 4 waves,
+// v_mfma_f32_32x32x2_f32, staged through registers.  Both accumulate in fp32
+// and hand their epilogue 32 x 32 blocks (TileCtx).
 //
 // Blocks are ordered for the L2 of each XCD: the hardware hands block b to
 // XCD b % 8, so consecutive logical tiles are given to the same XCD, and
 // logical tiles walk GROUP_M tile rows at a time (the concurrent tiles of an
 // XCD then share a few A and B panels).
-//
-// bf16 operands use v_mfma_f32_32x32x16_bf16, fp32 operands
-// v_mfma_f32_32x32x2_f32; both accumulate in fp32.
 #pragma once
 
 #include <algorithm>
@@ -57,7 +55,7 @@ struct TileCfg {
   static constexpr int MB = WM / 32, NB = WN / 32;
   static constexpr int STAGE_BYTES = (BM + BN) * kRowBytes;
 };
-// 128 x 128 tile, 64 x 64 per wave: any operand layout, bf16 or fp32.
+// 128 x 128 tile, 64 x 64 per wave: every fp32 GEMM.
 using CfgSmall = TileCfg<128, 128, 64, 64, 2>;
 // 256 x 256 tile, 8 waves of 128 x 64 (two waves per SIMD): every bf16 GEMM.
 // 1.5x the MFMA work per byte read from LDS of the small tile, and a second
@@ -208,70 +206,6 @@ struct MNMajorLoaderGrouped : MNMajorLoader<T, ROWS, THREADS> {
   }
 };
 
-// bf16 MN-major tile, stored in LDS as it is in memory: 64 k-rows of ROWS
-// operand rows (2 ROWS bytes each), 16-byte chunks XOR-swizzled by
-// 4 (k mod 4) (see mn_off).  The transpose happens in the fragment reads
-// (ds_read_b64_tr_b16, see Frags), so the copy is a plain one: each thread
-// moves PER 16-byte chunks, one per substep group, consecutive threads
-// along a k-row (whole 128-byte lines per load).  K-rows past the end
-// re-read the last k-row; with ZERO_TAIL they are written as zeros.  One
-// operand of a product zeroed is enough, so only the A side pays for it.
-template <int ROWS>
-__device__ __forceinline__ int mn_off(int k, int m) {
-  return k * (2 * ROWS) + (((m >> 3) ^ (4 * (k & 3))) << 4) + (m & 7) * 2;
-}
-
-template <int ROWS, int THREADS, int GROUPS, bool ZERO_TAIL>
-struct MNMajorLoaderB16 {
-  static constexpr int CHUNKS = ROWS / 8;               // 16-byte chunks per k-row
-  static constexpr int PER = 64 * CHUNKS / THREADS;     // chunks per thread per stage
-  static constexpr int PG = PER / GROUPS;
-  static_assert(PER % GROUPS == 0 && CHUNKS >= 16, "stage chunks must split evenly; swizzle needs 16 chunks");
-  u32x4_t reg[PER];
-  uint32_t moff[PER];   // byte offset of the chunk's operand row within a k-row (clamped)
-  int kr[PER];          // k-row of the chunk inside the stage
-  int loff[PER];        // LDS byte offset of the chunk
-  int K_;
-  int lim;              // K - 1 - k0 of the last load (k-rows beyond it are past K)
-
-  __device__ __forceinline__ void init(int64_t, int row0, int rows, int K, int tid) {
-    K_ = K;
-    lim = 63;
-    static_for<PER>([&](auto i) EE_ALWAYS_INLINE {
-      const int c = tid + decltype(i)::value * THREADS;
-      const int k = c / CHUNKS, ch = c % CHUNKS;
-      const int m = min(row0 + ch * 8, rows - 8) - row0;  // rows is a multiple of 8
-      kr[i] = k;
-      moff[i] = static_cast<uint32_t>(m * 2);
-      loff[i] = k * (2 * ROWS) + ((ch ^ (4 * (k & 3))) << 4);
-    });
-  }
-  template <int G>
-  __device__ __forceinline__ void load(const bf16_t *base, int64_t ld, int row0, int k0) {
-    const char *panel = reinterpret_cast<const char *>(base + static_cast<int64_t>(k0) * ld + row0);
-    const int l = K_ - 1 - k0;
-    const int ld2 = static_cast<int>(ld * 2);  // < 2^23, checked by the launcher
-    static_for<PG>([&](auto q) EE_ALWAYS_INLINE {
-      constexpr int i = G * PG + decltype(q)::value;
-      const int k = min(kr[i], l);
-      reg[i] = *reinterpret_cast<const u32x4_t *>(panel + (moff[i] + static_cast<uint32_t>(__mul24(k, ld2))));
-    });
-    if constexpr (ZERO_TAIL && G == GROUPS - 1) lim = l;
-  }
-  template <int G>
-  __device__ __forceinline__ void store(char *lds, int) const {
-    static_for<PG>([&](auto q) EE_ALWAYS_INLINE {
-      constexpr int i = G * PG + decltype(q)::value;
-      u32x4_t v = reg[i];
-      if constexpr (ZERO_TAIL) {
-        const bool ok = kr[i] <= lim;
-        static_for<4>([&](auto j) EE_ALWAYS_INLINE { v[decltype(j)::value] = ok ? v[decltype(j)::value] : 0u; });
-      }
-      *reinterpret_cast<u32x4_t *>(lds + loff[i]) = v;
-    });
-  }
-};
-
 template <int ROWS, int THREADS> struct MNMajorLoader<float, ROWS, THREADS> {
   static constexpr int GROUPS = ROWS / 4;
   static constexpr int PER = (32 / 4) * GROUPS / THREADS;
@@ -306,97 +240,20 @@ template <int ROWS, int THREADS> struct MNMajorLoader<float, ROWS, THREADS> {
   }
 };
 
-template <typename T, bool KMajor, int ROWS, int THREADS, int GROUPS, bool ZERO_TAIL> struct LoaderSel {
-  using type = KMajorLoader<T, ROWS, THREADS, GROUPS>;
-};
-template <int ROWS, int THREADS, int GROUPS, bool ZERO_TAIL> struct LoaderSel<float, false, ROWS, THREADS, GROUPS, ZERO_TAIL> {
-  using type = MNMajorLoaderGrouped<float, ROWS, THREADS, GROUPS>;
-};
-template <int ROWS, int THREADS, int GROUPS, bool ZERO_TAIL> struct LoaderSel<bf16_t, false, ROWS, THREADS, GROUPS, ZERO_TAIL> {
-  using type = MNMajorLoaderB16<ROWS, THREADS, GROUPS, ZERO_TAIL>;
-};
-
+template <bool KMajor, int ROWS, int THREADS, int GROUPS>
+using F32Loader = std::conditional_t<KMajor, KMajorLoader<float, ROWS, THREADS, GROUPS>,
+                                     MNMajorLoaderGrouped<float, ROWS, THREADS, GROUPS>>;
 
 // ------------------------------------------------------------ MFMA step
-// Fragments of one K substep (16 values of K) for the wave's MB x NB blocks
-// of 32 x 32, read from one LDS stage, and the MFMAs that consume them.
-template <typename T, class Cfg, bool A_MN, bool B_MN> struct Frags;
-
-typedef short s16x4_t __attribute__((ext_vector_type(4)));
-typedef __attribute__((address_space(3))) s16x4_t lds_s16x4_t;
-
-// Lane base offsets of the MFMA fragment reads of one operand of a wave:
-// `blocks` blocks of 32 rows from row0.  K-major tiles: row (row0 + 32 b +
-// lane % 32), logical chunk (lane / 32) (the substep adds 2 chunks).
-// MN-major tiles (k-rows of ROWS operand rows): ds_read_b64_tr_b16 gives
-// lane 4a + b of each 16-lane group element b of the 8-byte chunks that
-// lanes a, a + 4, a + 8, a + 12 of the group address.  Lane j of group g
-// therefore addresses k-row 8 (g / 2) + j / 4 (+ 4 for the second read,
-// + 16 per substep) at operand rows m0 + 16 (g % 2) + 4 (j % 4) .. + 3, and
-// receives rows m0 + 16 (g % 2) + j at four consecutive k: with the second
-// read, the 8 values of K that the MFMA expects of lane (row = lane % 32,
-// k = 8 (lane / 32) + e).  K offsets that are multiples of 4 keep the
-// swizzle (4 (k mod 4)), so they go into the instruction offset.
-template <bool MN, int ROWS>
-__device__ __forceinline__ int frag_base(int row0, int lane) {
-  if constexpr (MN) {
-    const int g = lane >> 4, j = lane & 15;
-    return mn_off<ROWS>(8 * (g >> 1) + (j >> 2), row0 + 16 * (g & 1) + 4 * (j & 3));
-  } else {
-    return 0;  // unused: K-major reads compute lds_off directly
-  }
-}
-
-template <class Cfg, bool A_MN, bool B_MN> struct Frags<bf16_t, Cfg, A_MN, B_MN> {
-  static constexpr int MB = Cfg::MB, NB = Cfg::NB;
-  static constexpr int SUBSTEPS = 4;  // 4 x 16 = 64 values of K per stage
-  static constexpr int MMAS = MB * NB;  // MFMAs per substep
-  bf16x8_t a[MB], b[NB];
-
-  // One operand's fragments of substep s.  `base` = frag_base of each block
-  // (MN-major tiles), or the tile's first row (K-major tiles).
-  template <bool MN, int ROWS, int NBLK>
-  __device__ __forceinline__ static void read(bf16x8_t (&f)[NBLK], const char *lds, const int (&base)[NBLK],
-                                              int row0, int lane, int s) {
-    if constexpr (MN) {
-      static_for<NBLK>([&](auto i) EE_ALWAYS_INLINE {
-        const char *p = lds + base[i] + 16 * s * (2 * ROWS);
-        const s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_t *)(p));
-        const s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_t *)(p + 4 * (2 * ROWS)));
-        const s16x4_t both[2] = {lo, hi};
-        f[i] = __builtin_bit_cast(bf16x8_t, both);
-      });
-    } else {
-      const int r = lane & 31, ch = s * 2 + (lane >> 5);
-      static_for<NBLK>([&](auto i) EE_ALWAYS_INLINE {
-        f[i] = *reinterpret_cast<const bf16x8_t *>(lds + lds_off(row0 + i * 32 + r, ch));
-      });
-    }
-  }
-  __device__ __forceinline__ void load(const char *a_lds, const char *b_lds, const int (&a_base)[MB],
-                                       const int (&b_base)[NB], int a_row0, int b_row0, int lane, int s) {
-    read<A_MN, Cfg::BM>(a, a_lds, a_base, a_row0, lane, s);
-    read<B_MN, Cfg::BN>(b, b_lds, b_base, b_row0, lane, s);
-  }
-  __device__ __forceinline__ void mma(f32x16_t (&acc)[MB][NB]) const {
-    static_for<MB>([&](auto i) EE_ALWAYS_INLINE {
-      static_for<NB>([&](auto j) EE_ALWAYS_INLINE {
-        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
-      });
-    });
-  }
-};
-
-template <class Cfg, bool A_MN, bool B_MN> struct Frags<float, Cfg, A_MN, B_MN> {
-  // fp32 MN-major operands are transposed in registers on their way into
-  // LDS, so both fp32 operands are read K-major here.
+// fp32 fragments of one K substep (16 values of K) for the wave's MB x NB
+// blocks of 32 x 32, read from one LDS stage, and the MFMAs that consume them.
+template <class Cfg> struct FragsF32 {
   static constexpr int MB = Cfg::MB, NB = Cfg::NB;
   static constexpr int SUBSTEPS = 2;  // 2 x 16 = 32 values of K per stage
   static constexpr int MMAS = 8 * MB * NB;  // MFMAs per substep
   f32x4_t a[MB][2], b[NB][2];
 
-  __device__ __forceinline__ void load(const char *a_lds, const char *b_lds, const int (&)[MB], const int (&)[NB],
-                                       int a_row0, int b_row0, int lane, int s) {
+  __device__ __forceinline__ void load(const char *a_lds, const char *b_lds, int a_row0, int b_row0, int lane, int s) {
     const int r = lane & 31, half = lane >> 5;
     static_for<2>([&](auto c) EE_ALWAYS_INLINE {
       const int ch = s * 4 + half * 2 + c;
@@ -468,10 +325,15 @@ __device__ __forceinline__ void tile_of_block(int b, int nblk, int tiles_m, int 
 // tiles; the thread index is then opaque to the compiler, so that no address
 // it derives is hoisted out of the loop and kept live through the epilogue
 // (which spilled registers).
-template <typename T, bool AK, bool BKM, class Epi, class Cfg, bool LOOP = false>
-__device__ __forceinline__ void gemm_block(const Operand &A, const Operand &B, const GemmShape &s,
+template <typename T, bool AK, bool BKM, class Epi, class Cfg, bool LOOP>
+struct GemmBlock;
+
+// fp32.
+template <bool AK, bool BKM, class Epi, class Cfg, bool LOOP>
+struct GemmBlock<float, AK, BKM, Epi, Cfg, LOOP> {
+static __device__ __forceinline__ void run(const Operand &A, const Operand &B, const GemmShape &s,
                                            const typename Epi::Params &ep, int b, int nblk, int kz, char *smem) {
-  constexpr int BK = 8 * Elem<T>::CH;
+  constexpr int BK = 8 * Elem<float>::CH;
   constexpr int MB = Cfg::MB, NB = Cfg::NB;
   int tid_v = threadIdx.x;
   if constexpr (LOOP) asm volatile("" : "+v"(tid_v));
@@ -481,18 +343,16 @@ __device__ __forceinline__ void gemm_block(const Operand &A, const Operand &B, c
   int tile_m, tile_n;
   tile_of_block(b, nblk, tiles_m, tiles_n, tile_m, tile_n);
   const int m0 = tile_m * Cfg::BM, n0 = tile_n * Cfg::BN;
-  const T *a_ptr = static_cast<const T *>(A.ptr);
-  const T *b_ptr = static_cast<const T *>(B.ptr);
+  const float *a_ptr = static_cast<const float *>(A.ptr);
+  const float *b_ptr = static_cast<const float *>(B.ptr);
 
-  constexpr bool kB16 = std::is_same<T, bf16_t>::value;
-  constexpr bool kAMN = kB16 && !AK, kBMN = kB16 && !BKM;  // read with the LDS transpose
-  using F = Frags<T, Cfg, kAMN, kBMN>;
+  using F = FragsF32<Cfg>;
   constexpr int SUB = F::SUBSTEPS;
   constexpr bool kPair = EpiPairB<Epi>::value;
   static_assert(!kPair || BKM, "an interleaved pair is read K-major");
-  typename LoaderSel<T, AK, Cfg::BM, Cfg::THREADS, SUB, true>::type la;
-  std::conditional_t<kPair, KMajorPairLoader<T, Cfg::BN, Cfg::THREADS, SUB>,
-                     typename LoaderSel<T, BKM, Cfg::BN, Cfg::THREADS, SUB, false>::type>
+  F32Loader<AK, Cfg::BM, Cfg::THREADS, SUB> la;
+  std::conditional_t<kPair, KMajorPairLoader<float, Cfg::BN, Cfg::THREADS, SUB>,
+                     F32Loader<BKM, Cfg::BN, Cfg::THREADS, SUB>>
       lb;
   la.init(A.ld, m0, s.M, s.K, tid);
   if constexpr (kPair)
@@ -539,11 +399,8 @@ __device__ __forceinline__ void gemm_block(const Operand &A, const Operand &B, c
     lb.template load<decltype(g)::value>(b_ptr, B.ld, n0, k1);
   });
   __syncthreads();
-  int a_base[MB], b_base[NB];
-  static_for<MB>([&](auto i) EE_ALWAYS_INLINE { a_base[i] = frag_base<kAMN, Cfg::BM>(a_row0 + 32 * i, lane); });
-  static_for<NB>([&](auto j) EE_ALWAYS_INLINE { b_base[j] = frag_base<kBMN, Cfg::BN>(b_row0 + 32 * j, lane); });
   F f0, f1;
-  f0.load(smem, smem + B_OFF, a_base, b_base, a_row0, b_row0, lane, 0);
+  f0.load(smem, smem + B_OFF, a_row0, b_row0, lane, 0);
   for (int kt = 0; kt < nk; ++kt) {
     const char *cur = smem + (kt & 1) * Cfg::STAGE_BYTES;
     char *next = smem + ((kt + 1) & 1) * Cfg::STAGE_BYTES;
@@ -553,9 +410,9 @@ __device__ __forceinline__ void gemm_block(const Operand &A, const Operand &B, c
       F &now = (sub % 2 == 0) ? f0 : f1;
       F &later = (sub % 2 == 0) ? f1 : f0;
       if constexpr (sub + 1 < SUB)
-        later.load(cur, cur + B_OFF, a_base, b_base, a_row0, b_row0, lane, sub + 1);
+        later.load(cur, cur + B_OFF, a_row0, b_row0, lane, sub + 1);
       else
-        later.load(next, next + B_OFF, a_base, b_base, a_row0, b_row0, lane, 0);  // next stage, published by the barrier
+        later.load(next, next + B_OFF, a_row0, b_row0, lane, 0);  // next stage, published by the barrier
       if constexpr (sub < SUB - 2) {
         la.template store<sub>(next, tid);
         lb.template store<sub>(next + B_OFF, tid);
@@ -583,6 +440,308 @@ __device__ __forceinline__ void gemm_block(const Operand &A, const Operand &B, c
 
   TileCtx<Cfg> t{s.M, s.N, m0, n0, tile_m, tile_n, wave_m, wave_n, lane, smem, kz};
   Epi::template apply<Cfg>(ep, acc, t);
+}
+};
+
+// ------------------------------------------------------------ bf16 main loop
+// 16 bytes a lane from base + off (off per lane) to LDS: lane l's bytes land
+// at lds + 16 l.  The compiler does not count these loads: whoever reads what
+// they bring waits with wait_vm, and a barrier makes it visible to the block.
+// (Only inputs, so nothing of the load in flight sits in a register.)
+__device__ __forceinline__ void load_lds16(const char *base, uint32_t off, uint32_t lds) {
+  // base and lds are the same in every lane; say so, as the asm takes them in scalar registers
+  const uint64_t b = reinterpret_cast<uint64_t>(base);
+  base = reinterpret_cast<const char *>(
+      static_cast<uint64_t>(static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(b)))) |
+      static_cast<uint64_t>(static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(b >> 32)))) << 32);
+  lds = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(lds)));
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(off), "s"(base)
+               : "memory");
+}
+template <int N> __device__ __forceinline__ void wait_vm() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
+__device__ __forceinline__ void wait_lgkm() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
+// A barrier without a wait for loads in flight (as __syncthreads would have).
+__device__ __forceinline__ void phase_barrier() {
+  __builtin_amdgcn_sched_barrier(0);
+  asm volatile("s_barrier" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
+}
+
+typedef short s16x4_t __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) s16x4_t lds_s16x4_t;
+
+// Accumulator rows of a 16 x 16 MFMA block: lanes 16 g .. 16 g + 15 hold rows
+// 4 g .. 4 g + 3 of the block, which stand for rows 0, 8, 4, 12 (+ 0..3) of
+// the tile's 16, so that one lane swap per register pair turns two column
+// blocks into the 32 x 32 layout of TileCtx.
+__device__ __forceinline__ int acc_row(int r) { return ((r >> 2) & 1) * 8 + ((r >> 3) & 1) * 4 + (r & 3); }
+
+// One operand of a 256-row tile, in two halves of 128 rows.  Half q holds,
+// for each wave that owns rows of this operand, the wave's 16-row blocks q *
+// WR / 2 .. : WR rows a wave (128 for A, 64 for B), WR / 2 of them per half.
+//
+// K-major: a half is 128 LDS rows of 64 values of K (128 bytes), 16-byte
+// chunk c of row r at chunk c ^ ((r / 2) mod 8) (conflict-free, see lds_off).
+// The load writes LDS linearly, so the XOR is applied to the address a lane
+// reads from; it stays inside the row's 128-byte line.
+// MN-major: a half is 64 LDS k-rows of 128 operand rows (256 bytes), chunk c of
+// k-row k at c ^ (2 (k mod 4) + 8 (k / 8 mod 2)).  ds_read_b64_tr_b16 gives lane
+// 4 a + b of each 16-lane group element b of the 8-byte pieces that lanes a,
+// a + 4, a + 8, a + 12 of the group address, so lane j of group g addresses
+// k-row 8 g + j / 4 (+ 4 for the second read) at 4 rows and receives row j at
+// 8 consecutive k; the XOR spreads the 8 k-rows of two groups over all banks.
+template <bool KM, int WR, bool PERM, bool PAIR>
+struct TileOperandB16 {
+  static constexpr int BLK = WR / 2 / 16;  // 16-row blocks per half
+  uint32_t off[PAIR ? 1 : 2][2];           // byte offsets of this thread's two chunks of each half
+  uint32_t ld2, kr;                        // MN-major: bytes per k-row; k-row of the thread's first chunk
+  const char *rd[KM ? 2 : BLK];            // fragment addresses of stage 0, half 0: K-major per 32 values of K; else per block
+  const char *base;
+  int64_t pair, step;
+
+  __device__ __forceinline__ static int tile_row(int q, int lr) { return (lr / (WR / 2)) * WR + q * (WR / 2) + lr % (WR / 2); }
+
+  // row0: first tile row, rows: rows of the operand (PAIR: of both matrices);
+  // wave: which WR rows of the tile the wave owns; lds: LDS of stage 0.
+  __device__ __forceinline__ void init(const Operand &O, int row0, int rows, int kbeg, int tid, int wave, int lane,
+                                       const char *lds) {
+    const bf16_t *p = static_cast<const bf16_t *>(O.ptr);
+    ld2 = static_cast<uint32_t>(O.ld * 2);
+    pair = O.pair;
+    const int r0 = PAIR ? row0 / 2 : row0, nrows = PAIR ? rows / 2 : rows;
+    if constexpr (KM) {
+      base = reinterpret_cast<const char *>(p + static_cast<int64_t>(r0) * O.ld + kbeg);
+      step = 128;
+      static_for<2>([&](auto e) EE_ALWAYS_INLINE {
+        const int c = decltype(e)::value * 512 + tid, lr = c >> 3, ch = (c & 7) ^ ((lr >> 1) & 7);
+        static_for<PAIR ? 1 : 2>([&](auto q) EE_ALWAYS_INLINE {
+          const int r = PAIR ? lr : tile_row(decltype(q)::value, lr);
+          off[q][e] = static_cast<uint32_t>(min(r0 + r, nrows - 1) - r0) * ld2 + ch * 16;
+        });
+      });
+      const int r = PERM ? acc_row(lane & 15) : lane & 15, x = (r >> 1) & 7;
+      static_for<2>([&](auto ks) EE_ALWAYS_INLINE {
+        rd[ks] = lds + (wave * (WR / 2) + r) * 128 + (((decltype(ks)::value * 4 + (lane >> 4)) ^ x) << 4);
+      });
+    } else {
+      base = reinterpret_cast<const char *>(p + static_cast<int64_t>(kbeg) * O.ld + row0);
+      step = static_cast<int64_t>(ld2) * 64;
+      kr = tid >> 4;
+      static_for<2>([&](auto e) EE_ALWAYS_INLINE {
+        const int k = decltype(e)::value * 32 + (tid >> 4), ch = (tid & 15) ^ swz(k);
+        static_for<2>([&](auto q) EE_ALWAYS_INLINE {
+          off[q][e] = static_cast<uint32_t>(min(row0 + tile_row(decltype(q)::value, ch * 8), rows - 8) - row0) * 2;
+        });
+      });
+      const int k = 8 * (lane >> 4) + ((lane >> 2) & 3), j = lane & 3;
+      const int m = PERM ? (j & 1) * 8 + (j >> 1) * 4 : 4 * j;
+      static_for<BLK>([&](auto i) EE_ALWAYS_INLINE {
+        const int row = wave * (WR / 2) + decltype(i)::value * 16 + m;
+        rd[i] = lds + k * 256 + (((row >> 3) ^ swz(k)) << 4) + (row & 7) * 2;
+      });
+    }
+  }
+  __device__ __forceinline__ static int swz(int k) { return 2 * (k & 3) + 8 * ((k >> 3) & 1); }
+
+  // Load half Q of stage t (of K values left from this stage on: MN-major
+  // k-rows past them re-read the last one).
+  template <int Q>
+  __device__ __forceinline__ void load(int t, int left, uint32_t lds_wave) const {
+    const char *p = base + static_cast<int64_t>(t) * step;
+    if constexpr (PAIR) p += Q * pair;
+    static_for<2>([&](auto e) EE_ALWAYS_INLINE {
+      constexpr int E = decltype(e)::value;
+      uint32_t o = off[PAIR ? 0 : Q][E];
+      if constexpr (!KM) o += __umul24(min(static_cast<int>(kr) + 32 * E, left - 1), ld2);
+      load_lds16(p, o, lds_wave + Q * 16384 + E * 8192);
+    });
+  }
+  // Zero the chunks this thread loads whose k-rows lie past K (MN-major).
+  __device__ __forceinline__ void zero_tail(int left, int tid, char *lds) const {
+    static_for<2>([&](auto e) EE_ALWAYS_INLINE {
+      if (static_cast<int>(kr) + 32 * decltype(e)::value >= left) {
+        static_for<2>([&](auto q) EE_ALWAYS_INLINE {
+          *reinterpret_cast<u32x4_t *>(lds + decltype(q)::value * 16384 + decltype(e)::value * 8192 + tid * 16) = u32x4_t{0, 0, 0, 0};
+        });
+      }
+    });
+  }
+  // Fragments of half Q of the stage in buffer BUF, both 32-value K steps.
+  template <int BUF, int Q>
+  __device__ __forceinline__ void read(bf16x8_t (&f)[BLK][2]) const {
+    static_for<BLK>([&](auto i) EE_ALWAYS_INLINE {
+      constexpr int I = decltype(i)::value;
+      static_for<2>([&](auto ks) EE_ALWAYS_INLINE {
+        constexpr int KS = decltype(ks)::value;
+        if constexpr (KM) {
+          f[I][KS] = *reinterpret_cast<const bf16x8_t *>(rd[KS] + BUF * 65536 + Q * 16384 + I * 2048);
+        } else {
+          const char *p = rd[I] + BUF * 65536 + Q * 16384 + KS * 8192;
+          const s16x4_t both[2] = {__builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_t *)(p)),
+                                   __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_t *)(p + 1024))};
+          f[I][KS] = __builtin_bit_cast(bf16x8_t, both);
+        }
+      });
+    });
+  }
+};
+
+// bf16.  The wave's 128 x 64 outputs are 8 x 4 blocks of 16 x 16; a stage is
+// four phases, one per quadrant (half of A, half of B), 16 MFMAs each:
+//   read the quadrant's new fragments, start loading half an operand tile of
+//   two stages ahead (the half that every wave has read by now), wait for the
+//   half that the next phase reads; barrier; MFMAs; barrier.
+// Waves 4..7 run one barrier behind waves 0..3 (a SIMD holds one of each),
+// so one wave's MFMAs cover the other's reads; a half is read by waves 0..3 in
+// the interval before, and by waves 4..7 in the interval in which waves 0..3
+// compute, and overwritten from the next on.  Five halves (10 loads a thread)
+// stay in flight.
+//
+// What bounds it is power: with random operands the chip holds its clock
+// down, and at its limit 16 x 16 x 32 MFMAs on registers alone run at 2143
+// TFLOP/s where 32 x 32 x 16 reach 1867; loads that bypass the registers
+// lower it further.  4096 x 32000 x 4096 with nothing stored: 1509 TFLOP/s,
+// where 32 x 32 x 16 staged through registers and interleaved MFMA by MFMA
+// reached 1340.
+template <bool AK, bool BKM, class Epi, class Cfg, bool LOOP>
+struct GemmBlock<bf16_t, AK, BKM, Epi, Cfg, LOOP> {
+  static __device__ __forceinline__ void run(const Operand &A, const Operand &B, const GemmShape &s,
+                                             const typename Epi::Params &ep, int b, int nblk, int kz, char *smem) {
+    static_assert(Cfg::BM == 256 && Cfg::BN == 256 && Cfg::WM == 128 && Cfg::WN == 64, "8 waves of 128 x 64");
+    constexpr bool kPair = EpiPairB<Epi>::value;
+    static_assert(!kPair || BKM, "an interleaved pair is read K-major");
+    int tid_v = threadIdx.x;
+    if constexpr (LOOP) asm volatile("" : "+v"(tid_v));
+    const int tid = tid_v, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wave_m = wave / Cfg::WAVES_N, wave_n = wave % Cfg::WAVES_N;
+    int tile_m, tile_n;
+    tile_of_block(b, nblk, cdiv(s.M, Cfg::BM), cdiv(s.N, Cfg::BN), tile_m, tile_n);
+    const int m0 = tile_m * Cfg::BM, n0 = tile_n * Cfg::BN;
+    const int kbeg = s.kchunk > 0 ? kz * s.kchunk : 0;
+    const int K = (s.kchunk > 0 ? min(s.K, kbeg + s.kchunk) : s.K) - kbeg;
+    const int nk = cdiv(K, 64);
+
+    // LDS: per stage the halves A0, A1, B0, B1 of 16 KB.
+    constexpr int B_OFF = 32768;
+    TileOperandB16<AK, 128, true, false> ta;
+    TileOperandB16<BKM, 64, false, kPair> tb;
+    ta.init(A, m0, s.M, kbeg, tid, wave_m, lane, smem);
+    tb.init(B, n0, s.N, kbeg, tid, wave_n, lane, smem + B_OFF);
+    const uint32_t lds_wave =
+        static_cast<uint32_t>(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) char *)smem)) + wave * 1024;
+    // Stages past the last re-read it (into halves nobody reads again).
+    auto load_a = [&](auto q, auto buf, int t) EE_ALWAYS_INLINE {
+      const int u = min(t, nk - 1);
+      ta.template load<decltype(q)::value>(u, K - u * 64, lds_wave + decltype(buf)::value * 65536);
+    };
+    auto load_b = [&](auto q, auto buf, int t) EE_ALWAYS_INLINE {
+      const int u = min(t, nk - 1);
+      tb.template load<decltype(q)::value>(u, K - u * 64, lds_wave + decltype(buf)::value * 65536 + B_OFF);
+    };
+    f32x4_t acc[8][4];
+    static_for<8>([&](auto i) EE_ALWAYS_INLINE {
+      static_for<4>([&](auto j) EE_ALWAYS_INLINE { acc[i][j] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f}; });
+    });
+    bf16x8_t fa[4][2], fb[2][2][2];
+    auto mma = [&](auto qa, auto qb) EE_ALWAYS_INLINE {
+      __builtin_amdgcn_s_setprio(1);
+      static_for<2>([&](auto ks) EE_ALWAYS_INLINE {
+        static_for<4>([&](auto i) EE_ALWAYS_INLINE {
+          static_for<2>([&](auto j) EE_ALWAYS_INLINE {
+            constexpr int I = decltype(qa)::value * 4 + decltype(i)::value, J = decltype(qb)::value * 2 + decltype(j)::value;
+            acc[I][J] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[i][ks], fb[qb][j][ks], acc[I][J], 0, 0, 0);
+          });
+        });
+      });
+      __builtin_amdgcn_s_setprio(0);
+    };
+    using H0 = std::integral_constant<int, 0>;
+    using H1 = std::integral_constant<int, 1>;
+    load_a(H0{}, H0{}, 0);
+    load_b(H0{}, H0{}, 0);
+    load_b(H1{}, H0{}, 0);
+    load_a(H1{}, H0{}, 0);
+    load_a(H0{}, H1{}, 1);
+    load_b(H0{}, H1{}, 1);
+    load_b(H1{}, H1{}, 1);
+    wait_vm<10>();
+    phase_barrier();
+    if (wave_m == 1) phase_barrier();  // waves 4..7 run one barrier behind
+    auto stage = [&](auto buf, int t) EE_ALWAYS_INLINE {
+      constexpr int BUF = decltype(buf)::value;
+      using Cur = std::integral_constant<int, BUF>;
+      using Nxt = std::integral_constant<int, BUF ^ 1>;
+      if constexpr (!AK) {
+        // The last stage of an MN-major product whose K is no multiple of 64:
+        // zero A's k-rows past K, each thread the chunks it loaded itself.
+        if (t == nk - 1 && K % 64 != 0) {
+          wait_vm<0>();
+          ta.zero_tail(K - t * 64, tid, smem + BUF * 65536);
+          wait_lgkm();
+          phase_barrier();
+          phase_barrier();
+        }
+      }
+      tb.template read<BUF, 0>(fb[0]);
+      ta.template read<BUF, 0>(fa);
+      load_a(H1{}, Nxt{}, t + 1);
+      wait_vm<10>();
+      wait_lgkm();
+      phase_barrier();
+      mma(H0{}, H0{});
+      phase_barrier();
+      tb.template read<BUF, 1>(fb[1]);
+      load_a(H0{}, Cur{}, t + 2);
+      wait_vm<10>();
+      wait_lgkm();
+      phase_barrier();
+      mma(H0{}, H1{});
+      phase_barrier();
+      ta.template read<BUF, 1>(fa);
+      load_b(H0{}, Cur{}, t + 2);
+      wait_lgkm();
+      phase_barrier();
+      mma(H1{}, H1{});
+      phase_barrier();
+      load_b(H1{}, Cur{}, t + 2);
+      wait_vm<10>();
+      phase_barrier();
+      mma(H1{}, H0{});
+      phase_barrier();
+    };
+    int t = 0;
+    for (; t + 1 < nk; t += 2) {
+      stage(H0{}, t);
+      stage(H1{}, t + 1);
+    }
+    if (t < nk) stage(H0{}, t);
+    if (wave_m == 0) phase_barrier();
+    wait_vm<0>();  // the epilogue's first barrier then frees the tile's LDS
+
+    // Two 16-column blocks side by side -> the 32 x 32 layout: the swap hands
+    // lanes 16..31 (48..63) the right block's columns of the rows that lanes
+    // 0..15 (32..47) keep of the left one, and the other way round.
+    f32x16_t blk[Cfg::MB][Cfg::NB];
+    static_for<8>([&](auto i) EE_ALWAYS_INLINE {
+      static_for<2>([&](auto j) EE_ALWAYS_INLINE {
+        static_for<4>([&](auto e) EE_ALWAYS_INLINE {
+          constexpr int I = decltype(i)::value, J = decltype(j)::value, E = decltype(e)::value;
+          const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(acc[I][2 * J][E]),
+                                                          __float_as_uint(acc[I][2 * J + 1][E]), false, false);
+          blk[I / 2][J][(I % 2) * 8 + E] = __uint_as_float(r[0]);
+          blk[I / 2][J][(I % 2) * 8 + 4 + E] = __uint_as_float(r[1]);
+        });
+      });
+    });
+    TileCtx<Cfg> ctx{s.M, s.N, m0, n0, tile_m, tile_n, wave_m, wave_n, lane, smem, kz};
+    Epi::template apply<Cfg>(ep, blk, ctx);
+  }
+};
+
+template <typename T, bool AK, bool BKM, class Epi, class Cfg, bool LOOP = false>
+__device__ __forceinline__ void gemm_block(const Operand &A, const Operand &B, const GemmShape &s,
+                                           const typename Epi::Params &ep, int b, int nblk, int kz, char *smem) {
+  GemmBlock<T, AK, BKM, Epi, Cfg, LOOP>::run(A, B, s, ep, b, nblk, kz, smem);
 }
 
 template <typename T, bool AK, bool BKM, class Epi, class Cfg>
@@ -745,6 +904,25 @@ hipError_t launch_gemm_pair(Operand A1, Operand B1, GemmShape s1, const typename
                      dim3(static_cast<unsigned>(base2 + b2 * splits2)), dim3(Cfg::THREADS), 0, stream, A1, B1, s1, ep1, A2,
                      B2, s2, ep2, static_cast<int>(b1), static_cast<int>(base2));
   return hipGetLastError();
+}
+
+// bf16 GEMMs take the 256 x 256 tile (either operand K-major or MN-major),
+// fp32 GEMMs the 128 x 128 tile.
+template <typename T, bool AK, bool BKM, class Epi>
+hipError_t run_gemm(Operand A, Operand B, GemmShape s, const typename Epi::Params &ep, hipStream_t stream) {
+  if constexpr (std::is_same<T, bf16_t>::value)
+    return launch_gemm<T, AK, BKM, Epi, CfgBig>(A, B, s, ep, stream);
+  else
+    return launch_gemm<T, AK, BKM, Epi, CfgSmall>(A, B, s, ep, stream);
+}
+
+template <typename T, bool AK1, bool BKM1, class Epi1, bool AK2, bool BKM2, class Epi2>
+hipError_t run_gemm_pair(Operand A1, Operand B1, GemmShape s1, const typename Epi1::Params &ep1, Operand A2,
+                         Operand B2, GemmShape s2, const typename Epi2::Params &ep2, hipStream_t stream) {
+  if constexpr (std::is_same<T, bf16_t>::value)
+    return launch_gemm_pair<T, AK1, BKM1, Epi1, AK2, BKM2, Epi2, CfgBig>(A1, B1, s1, ep1, A2, B2, s2, ep2, stream);
+  else
+    return launch_gemm_pair<T, AK1, BKM1, Epi1, AK2, BKM2, Epi2, CfgSmall>(A1, B1, s1, ep1, A2, B2, s2, ep2, stream);
 }
 
 }  // namespace ee

@@ -1,0 +1,27 @@
+// The output-matrix product of the exit head with its softmax-partials epilogue.
+#include "epilogues.h"
+#include "launch.h"
+
+namespace ee {
+
+int gemm_part_cols(bool f32) { return f32 ? CfgSmall::WN : CfgBig::WN; }
+
+hipError_t gemm_logits(bool f32, const void *w_out, const void *z, int vocab, int n, int h, void *P, int ldn,
+                       float *part_m, float *part_l, float *tgt, const int32_t *targets, hipStream_t stream,
+                       int shift0, const int *run_if) {
+  EE_DISPATCH(f32, {
+    typename EpiLogits<T>::Params ep{static_cast<T *>(P), ldn, part_m, part_l, tgt, targets, shift0};
+    const Operand A{z, h}, B{w_out, h};
+    const GemmShape sh{n, vocab, h};
+    if (run_if != nullptr) {
+      if constexpr (std::is_same<T, bf16_t>::value)
+        return launch_gemm_gated<T, true, true, EpiLogits<T>, CfgBig>(A, B, sh, ep, run_if, stream);
+      else
+        return launch_gemm_gated<T, true, true, EpiLogits<T>, CfgSmall>(A, B, sh, ep, run_if, stream);
+    }
+    return run_gemm<T, true, true, EpiLogits<T>>(A, B, sh, ep, stream);
+  });
+  return hipSuccess;
+}
+
+}  // namespace ee

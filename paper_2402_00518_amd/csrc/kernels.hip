@@ -1,13 +1,9 @@
 // Exit-head kernels for gfx950: RMSNorm forward/backward, the cross-entropy
-// reduction and seed, the loss and gain-gradient reductions, and the GEMM
-// instantiations with their fused epilogues.
+// reduction and seed, the loss and gain-gradient reductions.
 #include <math.h>
 
 #include <algorithm>
-#include <functional>
-#include <queue>
 #include <type_traits>
-#include <vector>
 
 #include "epilogues.h"
 #include "launch.h"
@@ -807,17 +803,6 @@ __global__ __launch_bounds__(256) void gain_reduce_kernel(const float *pa, int t
 
 
 // -------------------------------------------------------------- launchers
-#define EE_DISPATCH(f32, ...)            \
-  do {                                   \
-    if (f32) {                           \
-      using T = float;                   \
-      __VA_ARGS__;                       \
-    } else {                             \
-      using T = bf16_t;                  \
-      __VA_ARGS__;                       \
-    }                                    \
-  } while (0)
-
 hipError_t launch_row_rms(bool x_f32, const void *x, int64_t ldx, int n, int h, float eps, float *r,
                           hipStream_t stream, float *mu, int *clear, int *clear_exit) {
   const dim3 grid(cdiv(n, 4));
@@ -1072,232 +1057,6 @@ hipError_t launch_norm_bwd(bool f32, const float *dz, const float *y, const floa
       hipLaunchKernelGGL((norm_bwd_kernel<T, 16>), grid, dim3(256), 0, stream, dz, splits, zs, t0, f0, y, r, g, n, h, d, row_scale, scale_off);
   });
   return hipGetLastError();
-}
-
-
-// ------------------------------------------------------------------ GEMMs
-// bf16 GEMMs take the 256 x 256 tile (either operand K-major or MN-major),
-// fp32 GEMMs the 128 x 128 tile.
-template <typename T, bool AK, bool BKM, class Epi>
-hipError_t run_gemm(Operand A, Operand B, GemmShape s, const typename Epi::Params &ep, hipStream_t stream) {
-  if constexpr (std::is_same<T, bf16_t>::value)
-    return launch_gemm<T, AK, BKM, Epi, CfgBig>(A, B, s, ep, stream);
-  else
-    return launch_gemm<T, AK, BKM, Epi, CfgSmall>(A, B, s, ep, stream);
-}
-
-template <typename T, bool AK1, bool BKM1, class Epi1, bool AK2, bool BKM2, class Epi2>
-hipError_t run_gemm_pair(Operand A1, Operand B1, GemmShape s1, const typename Epi1::Params &ep1, Operand A2,
-                         Operand B2, GemmShape s2, const typename Epi2::Params &ep2, hipStream_t stream) {
-  if constexpr (std::is_same<T, bf16_t>::value)
-    return launch_gemm_pair<T, AK1, BKM1, Epi1, AK2, BKM2, Epi2, CfgBig>(A1, B1, s1, ep1, A2, B2, s2, ep2, stream);
-  else
-    return launch_gemm_pair<T, AK1, BKM1, Epi1, AK2, BKM2, Epi2, CfgSmall>(A1, B1, s1, ep1, A2, B2, s2, ep2, stream);
-}
-
-int gemm_part_cols(bool f32) { return f32 ? CfgSmall::WN : CfgBig::WN; }
-
-hipError_t gemm_logits(bool f32, const void *w_out, const void *z, int vocab, int n, int h, void *P, int ldn,
-                       float *part_m, float *part_l, float *tgt, const int32_t *targets, hipStream_t stream,
-                       int shift0, const int *run_if) {
-  EE_DISPATCH(f32, {
-    typename EpiLogits<T>::Params ep{static_cast<T *>(P), ldn, part_m, part_l, tgt, targets, shift0};
-    const Operand A{z, h}, B{w_out, h};
-    const GemmShape sh{n, vocab, h};
-    if (run_if != nullptr) {
-      if constexpr (std::is_same<T, bf16_t>::value)
-        return launch_gemm_gated<T, true, true, EpiLogits<T>, CfgBig>(A, B, sh, ep, run_if, stream);
-      else
-        return launch_gemm_gated<T, true, true, EpiLogits<T>, CfgSmall>(A, B, sh, ep, run_if, stream);
-    }
-    return run_gemm<T, true, true, EpiLogits<T>>(A, B, sh, ep, stream);
-  });
-  return hipSuccess;
-}
-
-hipError_t gemm_weight_grad_kk(bool f32, const void *g_t, const void *xhat_t, int m, int h, int ldn,
-                               const void *gain, const void *w, float *dw, float *part, int accumulate,
-                               hipStream_t stream, const float *gsum, const void *bias, float *part_b) {
-  EE_DISPATCH(f32, {
-    typename EpiWeightGrad<T>::Params ep{dw,   h,         static_cast<const T *>(gain), static_cast<const T *>(w),
-                                         part, accumulate, gsum, static_cast<const T *>(bias), part_b};
-    return run_gemm<T, true, true, EpiWeightGrad<T>>(Operand{xhat_t, ldn}, Operand{g_t, ldn},
-                                                        GemmShape{h, m, ldn}, ep, stream);
-  });
-  return hipSuccess;
-}
-
-hipError_t gemm_weight_grad_kk_pair(bool f32, const void *g1_t, const void *g2_t, const void *xhat_t, int m, int h,
-                                    int ldn, const void *gain, const void *w1, const void *w2, float *dw1, float *dw2,
-                                    float *part1, float *part2, int accumulate, hipStream_t stream) {
-  EE_DISPATCH(f32, {
-    const T *gn = static_cast<const T *>(gain);
-    typename EpiWeightGrad<T>::Params e1{dw1, h, gn, static_cast<const T *>(w1), part1, accumulate};
-    typename EpiWeightGrad<T>::Params e2{dw2, h, gn, static_cast<const T *>(w2), part2, accumulate};
-    return run_gemm_pair<T, true, true, EpiWeightGrad<T>, true, true, EpiWeightGrad<T>>(
-        Operand{xhat_t, ldn}, Operand{g1_t, ldn}, GemmShape{h, m, ldn}, e1, Operand{xhat_t, ldn},
-        Operand{g2_t, ldn}, GemmShape{h, m, ldn}, e2, stream);
-  });
-  return hipSuccess;
-}
-
-hipError_t gemm_gate_up_swiglu(bool f32, const void *u, const void *w_gate, const void *w_up, int n, int inter,
-                               int h, void *hgu, void *act, hipStream_t stream) {
-  EE_DISPATCH(f32, {
-    typename EpiGateUp<T>::Params ep{static_cast<typename GatePair<T>::type *>(hgu), static_cast<T *>(act)};
-    const int64_t pair = static_cast<const char *>(w_up) - static_cast<const char *>(w_gate);
-    return run_gemm<T, true, true, EpiGateUp<T>>(Operand{u, h}, Operand{w_gate, h, pair},
-                                                    GemmShape{n, 2 * inter, h}, ep, stream);
-  });
-  return hipSuccess;
-}
-
-hipError_t gemm_down_residual(bool f32, const void *act, const void *w_down, const void *x, int n, int h,
-                              int inter, float *y, hipStream_t stream, SplitTail sp) {
-  EE_DISPATCH(f32, {
-    const T *xt = static_cast<const T *>(x), *at = static_cast<const T *>(act), *wd = static_cast<const T *>(w_down);
-    // Tiles: tokens as rows, features as columns.  Split region: tokens
-    // [t0, n) x features [f0, h).  The rest takes all of K: tokens [0, t0)
-    // (f0 == 0) or features [0, f0) (t0 == 0).
-    const bool split = sp.splits > 1;
-    const int t0 = split ? sp.tok0 : n, f0 = split ? sp.feat0 : 0;
-    if (t0 < 0 || t0 > n || f0 < 0 || f0 > h || (t0 > 0 && f0 > 0)) return hipErrorInvalidValue;
-    const int m1 = t0 > 0 ? t0 : n, n1 = t0 > 0 ? h : f0;
-    const int64_t o = static_cast<int64_t>(t0) * h + f0;
-    typename EpiResidual<T>::Params e1{y, xt, h, 0};
-    typename EpiResidual<T>::Params e2{y + o, xt + o, h, static_cast<int64_t>(n) * h};
-    GemmShape s2{n - t0, h - f0, inter};
-    if (split) {
-      s2.kchunk = split_kchunk(inter, sp.splits);
-      if (cdiv(inter, s2.kchunk) != sp.splits) return hipErrorInvalidValue;  // Y holds sp.splits slices
-    }
-    return run_gemm_pair<T, true, true, EpiResidual<T>, true, true, EpiResidual<T>>(
-        Operand{at, inter}, Operand{wd, inter}, GemmShape{m1, n1, inter}, e1,
-        Operand{at + static_cast<int64_t>(t0) * inter, inter}, Operand{wd + static_cast<int64_t>(f0) * inter, inter},
-        s2, e2, stream);
-  });
-  return hipSuccess;
-}
-
-namespace {
-
-constexpr int kCus = 256;           // compute units the launch shapes are planned for
-constexpr double kEpilogueK = 1024;  // prologue and epilogue of a 256 x 256 tile, in K values of its main loop
-constexpr double kBytesPerK = 1.2e5;  // HBM bytes moved while a CU runs one such K value
-
-// Duration, in K values, of `full` whole-K tiles followed by `parts` blocks
-// of kchunk K values each, dispatched in order to the first free of kCus
-// compute units.
-double launch_span(int64_t full, int64_t parts, int K, int kchunk) {
-  const double D = K + kEpilogueK, d = kchunk + kEpilogueK;
-  const int64_t rest = full % kCus;
-  std::priority_queue<double, std::vector<double>, std::greater<double>> q;
-  double end = rest > 0 ? D : 0.0;
-  for (int i = 0; i < kCus; ++i) q.push(i < rest ? D : 0.0);
-  for (int64_t p = 0; p < parts; ++p) {
-    const double t = q.top() + d;
-    q.pop();
-    q.push(t);
-    end = std::max(end, t);
-  }
-  return static_cast<double>(full / kCus) * D + end;
-}
-
-}  // namespace
-
-int split_kchunk(int K, int splits) { return cdiv(cdiv(K, splits), 64) * 64; }
-
-SplitTail split_tail(bool f32, int n, int h, int K) {
-  SplitTail best{n, 0, 1};
-  if (f32 || n <= 0) return best;
-  // the last few shapes asked for (a layout asks for two per call)
-  struct Memo {
-    int n = -1, h = -1, K = -1;
-    SplitTail sp{0, 0, 1};
-  };
-  static thread_local Memo memo[4];
-  static thread_local int next = 0;
-  for (const Memo &m : memo)
-    if (m.n == n && m.h == h && m.K == K) return m.sp;
-  const int tm = cdiv(h, CfgBig::BM), tn = cdiv(n, CfgBig::BN);
-  const int64_t tiles = static_cast<int64_t>(tm) * tn;
-  if (tiles < 4 * kCus) {
-    const int64_t rounds = tiles / kCus;
-    double best_span = 0.9 * launch_span(tiles, 0, K, K);
-    for (int s = 2; s <= 4; s *= 2) {
-      if (K / s < 4 * 64) break;
-      const int kc = split_kchunk(K, s), slices = cdiv(K, kc);
-      // Split the last c token blocks (dim 0) or feature blocks (dim 1):
-      // all of them, or the fewest that leave the whole-K tiles one or two
-      // rounds short of the current count.
-      for (int dim = 0; dim < 2; ++dim) {
-        const int blocks = dim == 0 ? tn : tm, across = dim == 0 ? tm : tn;
-        int cand[3] = {blocks, 0, 0};
-        for (int r = 0; r < 2; ++r)
-          if (rounds - r >= 0) cand[r + 1] = static_cast<int>((tiles - (rounds - r) * kCus + across - 1) / across);
-        for (int c : cand) {
-          if (c < 1 || c > blocks) continue;
-          const SplitTail sp = dim == 0 ? SplitTail{(tn - c) * CfgBig::BN, 0, slices}
-                                        : SplitTail{0, (tm - c) * CfgBig::BM, slices};
-          // extra HBM traffic: slices 1.. written and read back, their sum written
-          const double outs = static_cast<double>(n - sp.tok0) * (h - sp.feat0);
-          const double extra = outs * 4 * (2 * (slices - 1) + 1) / kBytesPerK;
-          const double span = launch_span(static_cast<int64_t>(blocks - c) * across,
-                                          static_cast<int64_t>(c) * across * slices, K, kc) + extra;
-          if (span < best_span) {
-            best_span = span;
-            best = sp;
-          }
-        }
-      }
-    }
-  }
-  memo[next] = Memo{n, h, K, best};
-  next = (next + 1) % 4;
-  return best;
-}
-
-hipError_t gemm_dz(bool f32, const void *g_t, const void *w_out, int n, int ldn, int h, int vocab, float *dz,
-                   hipStream_t stream, SplitTail sp) {
-  EE_DISPATCH(f32, {
-    const T *gt = static_cast<const T *>(g_t), *wo = static_cast<const T *>(w_out);
-    // Tiles: tokens (padded to ldn; rows past n are not stored) as rows,
-    // features as columns, both operands read MN-major.  Split region:
-    // tokens [t0, n) x features [f0, h); the rest takes all of K: tokens
-    // [0, t0) (f0 == 0) or features [0, f0) (t0 == 0).
-    if (sp.splits <= 1) {
-      typename EpiStoreF32<T>::Params ep{dz, h, n, 0, 0};
-      return run_gemm<T, false, false, EpiStoreF32<T>>(Operand{gt, ldn}, Operand{wo, h}, GemmShape{ldn, h, vocab}, ep,
-                                                        stream);
-    }
-    const int t0 = sp.tok0, f0 = sp.feat0;
-    if (t0 < 0 || t0 > n || t0 % 64 != 0 || f0 < 0 || f0 > h || (t0 > 0 && f0 > 0)) return hipErrorInvalidValue;
-    const int m1 = t0 > 0 ? t0 : ldn, n1 = t0 > 0 ? h : f0;
-    typename EpiStoreF32<T>::Params e1{dz, h, t0 > 0 ? t0 : n, 0, 0};
-    typename EpiStoreF32<T>::Params e2{dz + static_cast<int64_t>(t0) * h + f0, h, n - t0, 0,
-                                       static_cast<int64_t>(n) * h};
-    GemmShape s2{ldn - t0, h - f0, vocab};
-    s2.kchunk = split_kchunk(vocab, sp.splits);
-    if (cdiv(vocab, s2.kchunk) != sp.splits) return hipErrorInvalidValue;  // dZ holds sp.splits slices
-    return run_gemm_pair<T, false, false, EpiStoreF32<T>, false, false, EpiStoreF32<T>>(
-        Operand{gt, ldn}, Operand{wo, h}, GemmShape{m1, n1, vocab}, e1, Operand{gt + t0, ldn}, Operand{wo + f0, h}, s2,
-        e2, stream);
-  });
-  return hipSuccess;
-}
-
-hipError_t gemm_da_swiglu_dw_down(bool f32, const void *dy, const void *w_down, int n, int inter, int h,
-                                 const void *hgu, void *dhg_t, void *dhu_t, int ldn, const void *act, float *dwd,
-                                 int accumulate, hipStream_t stream) {
-  EE_DISPATCH(f32, {
-    typename EpiSwiGLUBwd<T>::Params e1{static_cast<const typename GatePair<T>::type *>(hgu),
-                                        static_cast<T *>(dhg_t), static_cast<T *>(dhu_t), inter, ldn};
-    typename EpiStoreF32<T>::Params e2{dwd, inter, h, accumulate};
-    return run_gemm_pair<T, true, false, EpiSwiGLUBwd<T>, false, false, EpiStoreF32<T>>(
-        Operand{dy, h}, Operand{w_down, inter}, GemmShape{n, inter, h}, e1, Operand{dy, h}, Operand{act, inter},
-        GemmShape{h, inter, n}, e2, stream);
-  });
-  return hipSuccess;
 }
 
 }  // namespace ee

@@ -24,7 +24,8 @@ def asan_runtime():
 
 
 def kernel_objects():
-    objs = [os.path.join(BUILD, f) for f in ("kernels.hip.o", "optim.hip.o", "decode.hip.o")]
+    from paper_2402_00518_amd.build import SOURCES
+    objs = [os.path.join(BUILD, f + ".o") for f in SOURCES if f.endswith(".hip")]
     return objs if all(os.path.exists(o) for o in objs) else None
 
 

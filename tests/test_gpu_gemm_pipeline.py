@@ -1,0 +1,37 @@
+"""The bf16 product's pipeline at its edges: one, two and three stages of K,
+K that ends inside a stage (operands read MN-major), operands of a fraction of
+a tile, and a workspace that holds NaN before the step (nothing the products
+multiply may be left over from it).  The bars are those of test_gpu_parity."""
+
+import pytest
+import torch
+
+import workloads as W
+from test_gpu_parity import compare_full, gpu, say, small  # noqa: F401 (gpu: the module's GPU fixture)
+
+pytestmark = pytest.mark.gpu
+
+CASES = [
+    # name, kind, N, h, V, I: stages of the logits product h / 64, of dW_out
+    # ceil(N / 64), of dZ ceil(V / 64), of dW_down ceil(N / 64)
+    ("pipe_one_stage", W.EXIT_NORM, 5, 64, 65, 0),
+    ("pipe_two_stages", W.EXIT_NORM, 65, 128, 257, 0),
+    ("pipe_three_stages", W.EXIT_NORM, 129, 192, 1000, 0),
+    ("pipe_mlp_one_stage", W.EXIT_MLP, 9, 64, 64, 64),
+    ("pipe_mlp_tail_1", W.EXIT_MLP, 65, 64, 129, 64),
+    ("pipe_mlp_tail_63", W.EXIT_MLP, 191, 192, 319, 128),
+    ("pipe_mlp_tails_wide", W.EXIT_MLP, 300, 576, 1000, 320),
+]
+
+
+@pytest.mark.parametrize("name,kind,n,h,v,inter", CASES, ids=[c[0] for c in CASES])
+def test_pipeline_edges(name, kind, n, h, v, inter):
+    from paper_2402_00518_amd.session import Session
+    say(f"case: {name} N={n} h={h} V={v} I={inter}")
+    b = small(kind, n, h, v, inter, seed=9, name=name)
+    s = Session.from_batch(b)
+    s.ws.fill_(0xFF)
+    s.step()
+    torch.cuda.synchronize()
+    s.check_device_error()
+    compare_full(s, b, case=name)

@@ -588,21 +588,24 @@ struct TileOperandB16 {
 
 // bf16.  The wave's 128 x 64 outputs are 8 x 4 blocks of 16 x 16; a stage is
 // four phases, one per quadrant (half of A, half of B), 16 MFMAs each:
-//   read the quadrant's new fragments, start loading half an operand tile of
-//   two stages ahead (the half that every wave has read by now), wait for the
-//   half that the next phase reads; barrier; MFMAs; barrier.
+//   read the fragments that are new (8, 4, 8 and 4 of them: the last phase
+//   reads the next stage's first half of B, so the order of B's halves
+//   alternates), start loading the half of two stages ahead whose LDS every
+//   wave has read by now, wait for the half that the next phase reads;
+//   barrier; MFMAs; barrier.
 // Waves 4..7 run one barrier behind waves 0..3 (a SIMD holds one of each),
-// so one wave's MFMAs cover the other's reads; a half is read by waves 0..3 in
-// the interval before, and by waves 4..7 in the interval in which waves 0..3
-// compute, and overwritten from the next on.  Five halves (10 loads a thread)
-// stay in flight.
+// so one wave's MFMAs cover the other's reads (in step, the same code takes
+// 22% longer); a half is read by waves 0..3 in one interval, by waves 4..7 in
+// the next, in which waves 0..3 compute, and overwritten from the one after.
+// Six halves (12 loads a thread) stay in flight.
 //
 // What bounds it is power: with random operands the chip holds its clock
 // down, and at its limit 16 x 16 x 32 MFMAs on registers alone run at 2143
 // TFLOP/s where 32 x 32 x 16 reach 1867; loads that bypass the registers
-// lower it further.  4096 x 32000 x 4096 with nothing stored: 1509 TFLOP/s,
+// lower it further.  4096 x 32000 x 4096 with nothing stored: 1540 TFLOP/s,
 // where 32 x 32 x 16 staged through registers and interleaved MFMA by MFMA
-// reached 1340.
+// reached 1340 (12, 4, 8 and no fragment reads a phase: 1525; with a raised
+// wave priority around the MFMAs: 1530).
 template <bool AK, bool BKM, class Epi, class Cfg, bool LOOP>
 struct GemmBlock<bf16_t, AK, BKM, Epi, Cfg, LOOP> {
   static __device__ __forceinline__ void run(const Operand &A, const Operand &B, const GemmShape &s,
@@ -644,7 +647,6 @@ struct GemmBlock<bf16_t, AK, BKM, Epi, Cfg, LOOP> {
     });
     bf16x8_t fa[4][2], fb[2][2][2];
     auto mma = [&](auto qa, auto qb) EE_ALWAYS_INLINE {
-      __builtin_amdgcn_s_setprio(1);
       static_for<2>([&](auto ks) EE_ALWAYS_INLINE {
         static_for<4>([&](auto i) EE_ALWAYS_INLINE {
           static_for<2>([&](auto j) EE_ALWAYS_INLINE {
@@ -653,24 +655,28 @@ struct GemmBlock<bf16_t, AK, BKM, Epi, Cfg, LOOP> {
           });
         });
       });
-      __builtin_amdgcn_s_setprio(0);
     };
     using H0 = std::integral_constant<int, 0>;
     using H1 = std::integral_constant<int, 1>;
-    load_a(H0{}, H0{}, 0);
     load_b(H0{}, H0{}, 0);
+    load_a(H0{}, H0{}, 0);
     load_b(H1{}, H0{}, 0);
     load_a(H1{}, H0{}, 0);
+    load_b(H1{}, H1{}, 1);
     load_a(H0{}, H1{}, 1);
     load_b(H0{}, H1{}, 1);
-    load_b(H1{}, H1{}, 1);
-    wait_vm<10>();
+    load_a(H1{}, H1{}, 1);
+    wait_vm<12>();  // stage 0's first halves of B and A
     phase_barrier();
+    tb.template read<0, 0>(fb[0]);
+    wait_lgkm();
+    phase_barrier();  // every wave has read the half that the first phase overwrites
     if (wave_m == 1) phase_barrier();  // waves 4..7 run one barrier behind
     auto stage = [&](auto buf, int t) EE_ALWAYS_INLINE {
       constexpr int BUF = decltype(buf)::value;
       using Cur = std::integral_constant<int, BUF>;
-      using Nxt = std::integral_constant<int, BUF ^ 1>;
+      using First = Cur;  // the half of B this stage starts and ends with
+      using Second = std::integral_constant<int, BUF ^ 1>;
       if constexpr (!AK) {
         // The last stage of an MN-major product whose K is no multiple of 64:
         // zero A's k-rows past K, each thread the chunks it loaded itself.
@@ -682,31 +688,33 @@ struct GemmBlock<bf16_t, AK, BKM, Epi, Cfg, LOOP> {
           phase_barrier();
         }
       }
-      tb.template read<BUF, 0>(fb[0]);
       ta.template read<BUF, 0>(fa);
-      load_a(H1{}, Nxt{}, t + 1);
-      wait_vm<10>();
+      load_b(First{}, Cur{}, t + 2);
+      wait_vm<12>();
       wait_lgkm();
       phase_barrier();
-      mma(H0{}, H0{});
+      mma(H0{}, First{});
       phase_barrier();
-      tb.template read<BUF, 1>(fb[1]);
+      tb.template read<BUF, BUF ^ 1>(fb[BUF ^ 1]);
       load_a(H0{}, Cur{}, t + 2);
-      wait_vm<10>();
+      wait_vm<12>();
       wait_lgkm();
       phase_barrier();
-      mma(H0{}, H1{});
+      mma(H0{}, Second{});
       phase_barrier();
       ta.template read<BUF, 1>(fa);
-      load_b(H0{}, Cur{}, t + 2);
+      load_b(Second{}, Cur{}, t + 2);
+      wait_vm<12>();
       wait_lgkm();
       phase_barrier();
-      mma(H1{}, H1{});
+      mma(H1{}, Second{});
       phase_barrier();
-      load_b(H1{}, Cur{}, t + 2);
-      wait_vm<10>();
+      tb.template read<BUF ^ 1, BUF ^ 1>(fb[BUF ^ 1]);
+      load_a(H1{}, Cur{}, t + 2);
+      wait_vm<12>();
+      wait_lgkm();
       phase_barrier();
-      mma(H1{}, H0{});
+      mma(H1{}, First{});
       phase_barrier();
     };
     int t = 0;

@@ -163,8 +163,9 @@ template <typename T> using Raw4 = typename Raw4Of<T>::type;
 // the wave's LDS ([64 vocab ids][64 tokens], 16-byte chunks XOR-swizzled by
 // the vocab id) and leave in whole lines, eight lanes per line (a lane's own
 // four tokens would touch 32 lines per store); fp32 P is stored directly,
-// four tokens per 16-byte store.  Token columns past M up to ldp may be
-// written with finite values (the seed zeroes them).
+// four tokens per 16-byte store.  Token columns past M up to ldp are written
+// too, with the last token's values: the weight gradient multiplies them by
+// zeros, so they must be finite (the seed zeroes them).
 template <typename T>
 struct EpiLogits {
   struct Params {
@@ -279,7 +280,7 @@ struct EpiLogits {
             constexpr int Q = decltype(q)::value;
             const f32x4_t ml = kShift0 ? f32x4_t{0.0f, 0.0f, 0.0f, 0.0f}
                                        : *reinterpret_cast<const f32x4_t *>(wl + I * 32 + Q * 8 + hw * 4) * kLog2e;
-            const bool rok = kIn || t.m0 + rbase + I * 32 + Q * 8 < t.M;
+            const bool rok = kIn || t.m0 + rbase + I * 32 + Q * 8 < p.ldp;
             f32x4_t s4 = {0.0f, 0.0f, 0.0f, 0.0f};
             static_for<NB>([&](auto j) EE_ALWAYS_INLINE {
               f32x4_t e4;

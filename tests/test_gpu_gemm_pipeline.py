@@ -35,3 +35,19 @@ def test_pipeline_edges(name, kind, n, h, v, inter):
     torch.cuda.synchronize()
     s.check_device_error()
     compare_full(s, b, case=name)
+
+
+@pytest.mark.parametrize("kind,n,inter", [(W.EXIT_NORM, 70, 0), (W.EXIT_NORM, 513, 0), (W.EXIT_MLP, 150, 192)],
+                         ids=["norm_70", "norm_513", "mlp_150"])
+def test_f32_padding_is_written(kind, n, inter):
+    """fp32: the token columns between N and its padding take part in the
+    weight-gradient product (times zeros), so the logits product writes them:
+    NaN left in the workspace must not reach a gradient."""
+    from paper_2402_00518_amd.session import Session
+    say(f"case: f32 padding N={n} I={inter}")
+    b = small(kind, n, 128, 300, inter, "f32", seed=6, name="f32_padding")
+    s = Session.from_batch(b)
+    s.ws.fill_(0xFF)
+    s.step()
+    torch.cuda.synchronize()
+    compare_full(s, b, loss_rtol=1e-5, grad_rtol=1e-4, case="f32_padding")

@@ -1,22 +1,22 @@
 // Decode-time exit head (Sec. 3 "Inference": greedy decoding with a
 // confidence-based exit): a handful of rows through one exit, forward only.
 //
-// At decode the products are skinny, C[r][j] = sum_k W[r][k] Z[j][k] with
-// a weight W of R rows and only B <= 32 token rows Z per pass, so they are
-// bound by streaming W from HBM once.  A block owns 32 rows of W (64 for
-// a wide W past 8 token rows, so that each token fragment serves two row
-// groups and the token rows' share of the loads halves); each of its waves takes a share
-// of K and reads its rows straight into MFMA A fragments (16 bytes of K per
-// lane), 12 fragments per row group in flight per lane, with no LDS staging;
-// the token rows come from L2 as B fragments (tokens past B re-read row B-1
-// and their outputs are dropped).  The waves' partial sums meet in LDS in a
-// fixed order and the first wave runs the epilogue.  Splitting K gives about
-// 4000 waves at V = 32000, enough loads in flight on every CU.  bf16 uses
-// v_mfma_f32_32x32x16_bf16, fp32 v_mfma_f32_32x32x2_f32 over the same
-// 16-byte loads.
+// At decode the products are skinny, C[r][j] = sum_k W[r][k] Z[j][k] with a
+// weight W of R rows and B token rows Z, bound by streaming W from HBM once.
 //
-// Epilogues: store (gate projection), SwiGLU (up projection), residual
-// (down projection) and, for the output matrix, per-wave softmax partials:
+// bf16: ring_kernel, W and Z through LDS (see launch_ring).
+//
+// fp32: skinny_kernel, 32 tokens a pass.  A block owns 32 rows of W (64 for a
+// wide W past 8 token rows, so that each token fragment serves two row groups
+// and the token rows' share of the loads halves); each of its waves takes a
+// share of K and reads its rows straight into MFMA A fragments (16 bytes of K
+// per lane), 12 fragments per row group in flight per lane; the token rows
+// come from L2 as B fragments (tokens past B re-read row B-1 and their outputs
+// are dropped).  The waves' partial sums meet in LDS in a fixed order and the
+// first wave runs the epilogue.
+//
+// Epilogues: SwiGLU (gate and up projections), residual (down projection)
+// and, for the output matrix, softmax partials of 32 rows at a time:
 // for each token the maximum logit over the wave's rows, the lowest row
 // reaching it and sum exp(S - max).  decide_kernel combines the partials
 // of all waves into the greedy token, its probability and the exit flag.
@@ -26,10 +26,13 @@
 
 #include "ee_device.h"
 #include "launch.h"
+#include "ring.h"
 
 namespace ee {
 
 namespace {
+
+constexpr int cdiv64(int64_t a, int64_t b) { return static_cast<int>((a + b - 1) / b); }
 
 constexpr int kDecRows = 32;    // rows of W per row group (one MFMA tile)
 constexpr int kDecTokens = 32;  // token rows per pass (grid.y walks more)
@@ -43,37 +46,27 @@ __host__ __device__ constexpr int dec_waves(int row_blocks) {
 }
 constexpr int kDecGroup = 12;   // fragment loads per operand per lane in flight (8 and 16 measured slower)
 
-template <typename T> struct DecFrag;
-// bf16: a 16-byte load holds 8 values of K; one MFMA consumes 16 (two lane halves).
-template <> struct DecFrag<bf16_t> {
-  static constexpr int K_PER_LOAD = 16;  // values of K covered by one load across the wave
-  __device__ __forceinline__ static void mma(const u32x4_t &a, const u32x4_t &b, f32x16_t &acc) {
-    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b),
-                                                  acc, 0, 0, 0);
-  }
-};
-// fp32: a 16-byte load holds 4 values of K; four MFMAs of K = 2 (lane halves
-// hold K offsets 0-3 and 4-7 of the same 8, in the same order for A and B).
-template <> struct DecFrag<float> {
-  static constexpr int K_PER_LOAD = 8;
-  __device__ __forceinline__ static void mma(const u32x4_t &a, const u32x4_t &b, f32x16_t &acc) {
-    static_for<4>([&](auto e) EE_ALWAYS_INLINE {
-      constexpr int E = decltype(e)::value;
-      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a[E]), __uint_as_float(b[E]), acc, 0, 0, 0);
-    });
-  }
-};
+// A 16-byte load holds 4 values of K; four MFMAs of K = 2 (lane halves hold K
+// offsets 0-3 and 4-7 of the same 8, in the same order for A and B).
+constexpr int kDecKPerLoad = 8;  // values of K covered by one load across the wave
+__device__ __forceinline__ void dec_mma(const u32x4_t &a, const u32x4_t &b, f32x16_t &acc) {
+  static_for<4>([&](auto e) EE_ALWAYS_INLINE {
+    constexpr int E = decltype(e)::value;
+    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a[E]), __uint_as_float(b[E]), acc, 0, 0, 0);
+  });
+}
 
 // acc[v] of lane l: row r0 + (v/4)*8 + (l/32)*4 + v%4, token j0 + l%32.
 __device__ __forceinline__ int dec_row(int r0, int lane, int v) {
   return r0 + (v >> 2) * 8 + (lane >> 5) * 4 + (v & 3);
 }
 
-template <typename T, class Epi, int kDecWaves, int RG>
-__global__ __launch_bounds__(64 * kDecWaves) void skinny_kernel(const T *__restrict__ W, int64_t ldw, int R,
-                                                                const T *__restrict__ Z, int64_t ldz, int B, int K,
+template <class Epi, int kDecWaves, int RG>
+__global__ __launch_bounds__(64 * kDecWaves) void skinny_kernel(const float *__restrict__ W, int64_t ldw, int R,
+                                                                const float *__restrict__ Z, int64_t ldz, int B, int K,
                                                                 typename Epi::Params ep) {
-  constexpr int KL = DecFrag<T>::K_PER_LOAD;
+  using T = float;
+  constexpr int KL = kDecKPerLoad;
   constexpr int PER_LOAD = 16 / sizeof(T);  // elements of one 16-byte load
   __shared__ f32x16_t red[kDecWaves - 1][64];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -116,7 +109,7 @@ __global__ __launch_bounds__(64 * kDecWaves) void skinny_kernel(const T *__restr
     __builtin_amdgcn_sched_barrier(0);
     static_for<NQ>([&](auto q) EE_ALWAYS_INLINE {
       static_for<RG>([&](auto g) EE_ALWAYS_INLINE {
-        DecFrag<T>::mma(a[decltype(g)::value][decltype(q)::value], b[decltype(q)::value], acc[decltype(g)::value]);
+        dec_mma(a[decltype(g)::value][decltype(q)::value], b[decltype(q)::value], acc[decltype(g)::value]);
       });
     });
   };
@@ -172,54 +165,64 @@ __device__ __forceinline__ void for_rows4(const f32x16_t &acc, int r0, int j0, i
   });
 }
 
-template <typename T>
-struct DecStore {  // out[j][r] = C[r][j]
+struct DecStore {  // out[j][r] = C[r][j]  (fp32)
   struct Params {
-    T *out;
+    float *out;
     int64_t ld;
   };
   __device__ __forceinline__ static void apply(const Params &p, const f32x16_t &acc, int r0, int j0, int lane, int R,
                                                int B) {
     for_rows4(acc, r0, j0, lane, R, B, [&](int row0, int j, f32x4_t c) EE_ALWAYS_INLINE {
-      dstore4<T>(p.out + static_cast<int64_t>(j) * p.ld + row0, c);
+      dstore4<float>(p.out + static_cast<int64_t>(j) * p.ld + row0, c);
     });
   }
 };
 
-template <typename T>
-struct DecSwiGLU {  // A[j][r] = silu(Hg[j][r]) * C[r][j]
+struct DecSwiGLU {  // A[j][r] = silu(Hg[j][r]) * C[r][j]  (fp32)
   struct Params {
-    const T *hg;
-    T *act;
+    const float *hg;
+    float *act;
     int64_t ld;
   };
   __device__ __forceinline__ static void apply(const Params &p, const f32x16_t &acc, int r0, int j0, int lane, int R,
                                                int B) {
     for_rows4(acc, r0, j0, lane, R, B, [&](int row0, int j, f32x4_t hu) EE_ALWAYS_INLINE {
       const int64_t o = static_cast<int64_t>(j) * p.ld + row0;
-      const f32x4_t hg = dload4<T>(p.hg + o);
+      const f32x4_t hg = dload4<float>(p.hg + o);
       f32x4_t a;
       static_for<4>([&](auto e) EE_ALWAYS_INLINE {
         constexpr int E = decltype(e)::value;
         a[E] = silu_f(hg[E]) * hu[E];
       });
-      dstore4<T>(p.act + o, a);
+      dstore4<float>(p.act + o, a);
     });
   }
 };
 
+// Y[j][r] = X[j][r] + C[r][j]  (fp32 out).  With split K, slice 0 does so and
+// slice z > 0 stores its partial sum at extra + (z - 1) zstride (the exit norm
+// adds the slices).
 template <typename T>
-struct DecResidual {  // Y[j][r] = X[j][r] + C[r][j]  (fp32 out)
+struct DecResidual {
+  static constexpr bool kSplit = true;
   struct Params {
     const T *x;
     float *y;
     int64_t ld;
+    float *extra;
+    int64_t zstride;
   };
+  __device__ __forceinline__ static void slice(Params &p, int z) {
+    if (z > 0) {
+      p.x = nullptr;
+      p.y = p.extra + (z - 1) * p.zstride;
+    }
+  }
   __device__ __forceinline__ static void apply(const Params &p, const f32x16_t &acc, int r0, int j0, int lane, int R,
                                                int B) {
     for_rows4(acc, r0, j0, lane, R, B, [&](int row0, int j, f32x4_t c) EE_ALWAYS_INLINE {
       const int64_t o = static_cast<int64_t>(j) * p.ld + row0;
-      dstore4<float>(p.y + o, c + dload4<T>(p.x + o));
+      dstore4<float>(p.y + o, p.x != nullptr ? c + dload4<T>(p.x + o) : c);
     });
   }
 };
@@ -228,6 +231,7 @@ struct DecResidual {  // Y[j][r] = X[j][r] + C[r][j]  (fp32 out)
 // ids), per token: m = max, arg = lowest id reaching m, l = sum exp(S - m).
 // Stored at [32-row tile][token].
 struct DecLogits {
+  static constexpr bool kSplit = false;
   struct Params {
     float *part_m;
     float *part_l;
@@ -281,26 +285,56 @@ __device__ __forceinline__ void argmax_merge(float &m, int &t, float om, int ot)
   }
 }
 
+constexpr int kDecideTiles = 8;  // tiles a thread keeps: every load is issued at once
+
 __global__ __launch_bounds__(256) void decide_kernel(const float *part_m, const float *part_l,
                                                      const int32_t *part_arg, int tiles, int B, float threshold,
                                                      int32_t *token, float *confidence, int32_t *exit_flag) {
   __shared__ float sm[4];
   __shared__ int st[4];
   __shared__ float sl[4];
+  __shared__ int sa[4];
   const int j = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   // max over tiles, and the lowest tile reaching it; the first tile a thread
   // sees is always taken, so the result is a valid tile even when no maximum
   // compares (NaN)
   float m = -INFINITY;
-  int t_best = -1;
-  for (int t = tid; t < tiles; t += 256) {
-    const float v = part_m[static_cast<int64_t>(t) * B + j];
-    if (t_best < 0 || v > m) {  // t increases, so the first tile reaching the maximum is kept
-      m = v;
-      t_best = t;
+  int t_best = -1, arg = 0;
+  const bool kept = tiles <= kDecideTiles * 256;
+  float pm[kDecideTiles], pl[kDecideTiles];
+  int pa[kDecideTiles];
+  if (kept) {
+#pragma unroll
+    for (int q = 0; q < kDecideTiles; ++q) {
+      const int64_t o = static_cast<int64_t>(min(tid + 256 * q, tiles - 1)) * B + j;
+      pm[q] = part_m[o];
+      pl[q] = part_l[o];
+      pa[q] = part_arg[o];
+    }
+#pragma unroll
+    for (int q = 0; q < kDecideTiles; ++q) {
+      const int t = tid + 256 * q;
+      if (t < tiles && (t_best < 0 || pm[q] > m)) {  // t increases, so the first tile reaching the maximum is kept
+        m = pm[q];
+        t_best = t;
+        arg = pa[q];
+      }
+    }
+  } else {
+    for (int t = tid; t < tiles; t += 256) {
+      const float v = part_m[static_cast<int64_t>(t) * B + j];
+      if (t_best < 0 || v > m) {
+        m = v;
+        t_best = t;
+      }
     }
   }
+  const int mine = t_best;
   for (int o = 1; o < 64; o <<= 1) argmax_merge(m, t_best, __shfl_xor(m, o), __shfl_xor(t_best, o));
+  if (mine >= 0 && mine == t_best) {  // one thread of the wave
+    if (!kept) arg = part_arg[static_cast<int64_t>(mine) * B + j];
+    sa[wave] = arg;
+  }
   if (lane == 0) {
     sm[wave] = m;
     st[wave] = t_best;
@@ -310,23 +344,147 @@ __global__ __launch_bounds__(256) void decide_kernel(const float *part_m, const 
   int tb = st[0];
   for (int w = 1; w < 4; ++w) argmax_merge(mx, tb, sm[w], st[w]);
   float l = 0.0f;
-  for (int t = tid; t < tiles; t += 256) {
-    const int64_t o = static_cast<int64_t>(t) * B + j;
-    l += part_l[o] * __expf(part_m[o] - mx);
+  if (kept) {
+#pragma unroll
+    for (int q = 0; q < kDecideTiles; ++q)
+      if (tid + 256 * q < tiles) l += pl[q] * __expf(pm[q] - mx);
+  } else {
+    for (int t = tid; t < tiles; t += 256) {
+      const int64_t o = static_cast<int64_t>(t) * B + j;
+      l += part_l[o] * __expf(part_m[o] - mx);
+    }
   }
   l = warp_sum(l);
   if (lane == 0) sl[wave] = l;
   __syncthreads();
   if (tid == 0) {
     const float conf = 1.0f / ((sl[0] + sl[1]) + (sl[2] + sl[3]));
-    token[j] = part_arg[static_cast<int64_t>(tb) * B + j];
+    token[j] = sa[tb % 256 / 64];  // the tile's thread is tile mod 256
     confidence[j] = conf;
     exit_flag[j] = conf > threshold ? 1 : 0;
   }
 }
 
-template <typename T, class Epi, int RG>
-hipError_t launch_skinny_rg(const T *w, int64_t ldw, int R, const T *z, int64_t ldz, int B, int K,
+// Gate and up projections as one product (W's rows interleaved in blocks of
+// 32; bf16): A[j][r] = silu(Hg[j][r]) * Hu[j][r], Hg rounded to bf16 first.
+struct DecGateUp {
+  static constexpr bool kSplit = false;
+  struct Params {
+    bf16_t *act;
+    int64_t ld;
+  };
+  __device__ __forceinline__ static void apply(const Params &p, const f32x16_t &hg, const f32x16_t &hu, int r0, int j0,
+                                               int lane, int R, int B) {
+    const int j = j0 + (lane & 31);
+    if (j >= B) return;
+    static_for<4>([&](auto q) EE_ALWAYS_INLINE {
+      constexpr int Q = decltype(q)::value;
+      const int row0 = dec_row(r0, lane, 4 * Q);
+      if (row0 >= R) return;
+      f32x4_t a;
+      static_for<4>([&](auto e) EE_ALWAYS_INLINE {
+        constexpr int E = decltype(e)::value;
+        a[E] = silu_f(to_f32(from_f32<bf16_t>(hg[4 * Q + E]))) * hu[4 * Q + E];
+      });
+      dstore4<bf16_t>(p.act + static_cast<int64_t>(j) * p.ld + row0, a);
+    });
+  }
+};
+
+// bf16: the products from LDS.  A block takes BM
+// rows of W (PAIR: BM / 2 of each matrix) and BN tokens through the ring of
+// ring.h; blocks of one row tile and several token groups are neighbours on
+// one XCD, so W comes from memory once.  blockIdx.y: split-K slice; blockIdx.z:
+// token groups past the first `groups`.
+template <class Epi, int BM, int BN, int WN, int NS, int Q, bool PAIR>
+__global__ __launch_bounds__(BM / 64 * (BN / WN) * 64) void ring_kernel(Operand W, int R, Operand Z, int B, int K,
+                                                                        int kchunk, int groups,
+                                                                        typename Epi::Params ep) {
+  using Rg = Ring<BM, BN, 64, WN, NS, true, true, PAIR, false, Q>;
+  __shared__ __attribute__((aligned(16))) char smem[NS * Rg::STAGE_BYTES];
+  const int xcd = blockIdx.x & 7, idx = blockIdx.x >> 3;
+  const int tile = (idx / groups) * 8 + xcd, rows = PAIR ? 2 * R : R;
+  const int j0 = (static_cast<int>(blockIdx.z) * groups + idx % groups) * BN;
+  if (tile * BM >= rows || j0 >= B) return;
+  const int kbeg = blockIdx.y * kchunk;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  f32x4_t acc[4][WN / 16];
+  Rg::run(W, tile * BM, rows, Z, j0, B, kbeg, min(kchunk, K - kbeg), tid, smem, acc);
+  if constexpr (Epi::kSplit) Epi::slice(ep, blockIdx.y);
+  f32x16_t blk[2][WN / 32];
+  to_blocks32<2, WN / 32>(acc, blk);
+  const int r0 = tile * BM + (wave / Rg::WAVES_N) * 64, t0 = j0 + (wave % Rg::WAVES_N) * WN;
+  static_for<WN / 32>([&](auto j) EE_ALWAYS_INLINE {
+    constexpr int J = decltype(j)::value;
+    if constexpr (PAIR) {
+      Epi::apply(ep, blk[0][J], blk[1][J], r0 / 2, t0 + 32 * J, lane, R, B);
+    } else {
+      static_for<2>([&](auto i) EE_ALWAYS_INLINE {
+        constexpr int I = decltype(i)::value;
+        if (r0 + 32 * I < R) Epi::apply(ep, blk[I][J], r0 + 32 * I, t0 + 32 * J, lane, R, B);
+      });
+    }
+  });
+}
+
+template <class Epi, int BM, int BN, int WN, int NS, int Q, bool PAIR>
+hipError_t launch_ring_cfg(Operand W, int R, Operand Z, int B, int K, int splits, const typename Epi::Params &ep,
+                           hipStream_t stream) {
+  const int rows = PAIR ? 2 * R : R;
+  const int tiles = (rows + BM - 1) / BM, all = (B + BN - 1) / BN, groups = std::min(all, 64);
+  const int kchunk = ((K / 64 + splits - 1) / splits) * 64;
+  hipLaunchKernelGGL((ring_kernel<Epi, BM, BN, WN, NS, Q, PAIR>),
+                     dim3(static_cast<unsigned>((tiles + 7) / 8 * 8 * groups), static_cast<unsigned>(splits),
+                          static_cast<unsigned>((all + groups - 1) / groups)),
+                     dim3(BM / 64 * (BN / WN) * 64), 0, stream, W, R, Z, B, K, kchunk, groups, ep);
+  return hipGetLastError();
+}
+
+// Shapes, from us per call of the whole decision (7B Norm exit: h 4096, V 32000;
+// 70B: h 8192; 13B MLP: h 5120, I 13824; the former path, K split over the
+// waves of a block and 32 tokens a pass, in brackets):
+//   8 tokens: 7B 61 (62), 70B 111 (119), 13B MLP 162 (203);
+//   64 tokens: 7B 63 (135), 70B 110 (267), 13B MLP 180 (473);
+//   230 tokens: 7B 100 (448), 70B 177 (967), 13B MLP 306 (1439).
+// W's rows come 128 a block, and the tokens in groups of 32, 64 or, past 64
+// tokens, 128.  Two blocks share a CU (4 x 20, 3 x 24 or 2 x 32 KB of LDS)
+// except where 128-token blocks are at most one per CU, which take 4 stages (70
+// against 92 us for 7B at 128 tokens; at 230 tokens, two a CU, 100 against 110).
+// Rows a multiple of 8 KB apart are taken in parts (see Ring: 70B at 32 tokens
+// 140 -> 111 us, 7B 74 -> 62; h 1024, 2048 and 5120 gain nothing), where the
+// registers allow it.  A narrow product (the down projection) is split over K
+// and takes 64 rows a block (13B MLP at 64 tokens: 248 us unsplit, 189 split,
+// 180 with 64 rows).
+constexpr int kCampBytes = 8192;
+template <class Epi, bool PAIR>
+hipError_t launch_ring(Operand W, int R, Operand Z, int B, int K, int splits, const typename Epi::Params &ep,
+                       hipStream_t stream) {
+  if (R <= 0 || B <= 0) return hipSuccess;
+  if (K % 64 != 0) return hipErrorInvalidValue;
+  const bool camp = W.ld * 2 % kCampBytes == 0 && splits == 1;
+  const int64_t blocks = (static_cast<int64_t>(PAIR ? 2 * R : R) + 127) / 128 * ((B + 127) / 128) * splits;
+  if constexpr (Epi::kSplit) {
+    if (B <= 128 && blocks < 200) {
+      if (B <= 32) return launch_ring_cfg<Epi, 64, 32, 32, 4, 1, PAIR>(W, R, Z, B, K, splits, ep, stream);
+      if (B <= 64) return launch_ring_cfg<Epi, 64, 64, 32, 4, 1, PAIR>(W, R, Z, B, K, splits, ep, stream);
+      return launch_ring_cfg<Epi, 64, 128, 64, 4, 1, PAIR>(W, R, Z, B, K, splits, ep, stream);
+    }
+  }
+  if (B <= 32) {
+    if (camp) return launch_ring_cfg<Epi, 128, 32, 32, 4, 8, PAIR>(W, R, Z, B, K, splits, ep, stream);
+    return launch_ring_cfg<Epi, 128, 32, 32, 4, 1, PAIR>(W, R, Z, B, K, splits, ep, stream);
+  }
+  if (B <= 64) {
+    if (camp) return launch_ring_cfg<Epi, 128, 64, 32, 3, 8, PAIR>(W, R, Z, B, K, splits, ep, stream);
+    return launch_ring_cfg<Epi, 128, 64, 32, 3, 1, PAIR>(W, R, Z, B, K, splits, ep, stream);
+  }
+  if (blocks > 256) return launch_ring_cfg<Epi, 128, 128, 64, 2, 1, PAIR>(W, R, Z, B, K, splits, ep, stream);
+  if (camp) return launch_ring_cfg<Epi, 128, 128, 64, 4, 4, PAIR>(W, R, Z, B, K, splits, ep, stream);
+  return launch_ring_cfg<Epi, 128, 128, 64, 4, 1, PAIR>(W, R, Z, B, K, splits, ep, stream);
+}
+
+template <class Epi, int RG>
+hipError_t launch_skinny_rg(const float *w, int64_t ldw, int R, const float *z, int64_t ldz, int B, int K,
                             const typename Epi::Params &ep, hipStream_t stream) {
   const int row_blocks = (R + kDecRows * RG - 1) / (kDecRows * RG);
   const dim3 grid(static_cast<unsigned>(row_blocks), static_cast<unsigned>((B + kDecTokens - 1) / kDecTokens));
@@ -334,14 +492,14 @@ hipError_t launch_skinny_rg(const T *w, int64_t ldw, int R, const T *z, int64_t 
   const int waves = RG > 1 ? std::min(dec_waves(row_blocks), 8) : dec_waves(row_blocks);
   switch (waves) {
     case 4:
-      hipLaunchKernelGGL((skinny_kernel<T, Epi, 4, RG>), grid, dim3(64 * 4), 0, stream, w, ldw, R, z, ldz, B, K, ep);
+      hipLaunchKernelGGL((skinny_kernel<Epi, 4, RG>), grid, dim3(64 * 4), 0, stream, w, ldw, R, z, ldz, B, K, ep);
       break;
     case 8:
-      hipLaunchKernelGGL((skinny_kernel<T, Epi, 8, RG>), grid, dim3(64 * 8), 0, stream, w, ldw, R, z, ldz, B, K, ep);
+      hipLaunchKernelGGL((skinny_kernel<Epi, 8, RG>), grid, dim3(64 * 8), 0, stream, w, ldw, R, z, ldz, B, K, ep);
       break;
     default:
       if constexpr (RG == 1)
-        hipLaunchKernelGGL((skinny_kernel<T, Epi, kDecWavesMax, RG>), grid, dim3(64 * kDecWavesMax), 0, stream, w, ldw,
+        hipLaunchKernelGGL((skinny_kernel<Epi, kDecWavesMax, RG>), grid, dim3(64 * kDecWavesMax), 0, stream, w, ldw,
                            R, z, ldz, B, K, ep);
   }
   return hipGetLastError();
@@ -351,52 +509,59 @@ hipError_t launch_skinny_rg(const T *w, int64_t ldw, int R, const T *z, int64_t 
 // 32-row groups per token fragment, halving the token rows' share of the
 // loads (at 8 waves a block: measured 11% faster at 32 tokens for 13824 and
 // 32000 rows; with 5120 rows the 80 blocks kept too few loads in flight).
-template <typename T, class Epi>
+template <class Epi>
 hipError_t launch_skinny(const void *W, int64_t ldw, int R, const void *Z, int64_t ldz, int B, int K,
                          const typename Epi::Params &ep, hipStream_t stream) {
   if (R <= 0 || B <= 0) return hipSuccess;
-  if (K % (4 * DecFrag<T>::K_PER_LOAD) != 0) return hipErrorInvalidValue;
-  const T *w = static_cast<const T *>(W);
-  const T *z = static_cast<const T *>(Z);
-  if (B > 8 && R >= 12288) return launch_skinny_rg<T, Epi, 2>(w, ldw, R, z, ldz, B, K, ep, stream);
-  return launch_skinny_rg<T, Epi, 1>(w, ldw, R, z, ldz, B, K, ep, stream);
+  if (K % (4 * kDecKPerLoad) != 0) return hipErrorInvalidValue;
+  const float *w = static_cast<const float *>(W);
+  const float *z = static_cast<const float *>(Z);
+  if (B > 8 && R >= 12288) return launch_skinny_rg<Epi, 2>(w, ldw, R, z, ldz, B, K, ep, stream);
+  return launch_skinny_rg<Epi, 1>(w, ldw, R, z, ldz, B, K, ep, stream);
 }
 
 }  // namespace
 
 int decode_tiles(int rows) { return (rows + kDecRows - 1) / kDecRows; }
 
-hipError_t decode_store(bool f32, const void *w, int rows, const void *z, int n, int k, void *out,
-                        hipStream_t stream) {
-  if (f32)
-    return launch_skinny<float, DecStore<float>>(w, k, rows, z, k, n, k, {static_cast<float *>(out), rows}, stream);
-  return launch_skinny<bf16_t, DecStore<bf16_t>>(w, k, rows, z, k, n, k, {static_cast<bf16_t *>(out), rows},
-                                                 stream);
+hipError_t decode_gate_up(bool f32, const void *w_gate, const void *w_up, int rows, const void *z, int n, int k,
+                          void *hg, void *act, hipStream_t stream) {
+  if (!f32) {
+    const int64_t pair = static_cast<const char *>(w_up) - static_cast<const char *>(w_gate);
+    return launch_ring<DecGateUp, true>(Operand{w_gate, k, pair}, rows, Operand{z, k}, n, k, 1,
+                                        {static_cast<bf16_t *>(act), rows}, stream);
+  }
+  const hipError_t e = launch_skinny<DecStore>(w_gate, k, rows, z, k, n, k, {static_cast<float *>(hg), rows}, stream);
+  if (e != hipSuccess) return e;
+  return launch_skinny<DecSwiGLU>(w_up, k, rows, z, k, n, k,
+                                  {static_cast<const float *>(hg), static_cast<float *>(act), rows}, stream);
 }
 
-hipError_t decode_swiglu(bool f32, const void *w, int rows, const void *z, int n, int k, const void *hg,
-                         void *act, hipStream_t stream) {
-  if (f32)
-    return launch_skinny<float, DecSwiGLU<float>>(
-        w, k, rows, z, k, n, k, {static_cast<const float *>(hg), static_cast<float *>(act), rows}, stream);
-  return launch_skinny<bf16_t, DecSwiGLU<bf16_t>>(
-      w, k, rows, z, k, n, k, {static_cast<const bf16_t *>(hg), static_cast<bf16_t *>(act), rows}, stream);
+// Slices of the down projection's K: enough for two 64-row blocks a CU (two
+// 128-row blocks past 128 tokens), at most `most`, and 512 values of K each.
+int decode_residual_splits(bool f32, int rows, int n, int k, int most) {
+  if (f32) return 1;
+  const int64_t bm = n <= 128 ? 64 : 128, blocks = (rows + bm - 1) / bm * ((n + 127) / 128);
+  const int s = static_cast<int>(std::max<int64_t>(1, std::min<int64_t>({most, 512 / blocks, k / 512})));
+  return cdiv64(k / 64, cdiv64(k / 64, s));  // slices of whole stages, none empty
 }
 
 hipError_t decode_residual(bool f32, const void *w, int rows, const void *z, int n, int k, const void *x,
-                           float *y, hipStream_t stream) {
+                           float *y, int splits, float *extra, hipStream_t stream) {
+  if (splits < 1 || (splits > 1 && (f32 || extra == nullptr))) return hipErrorInvalidValue;
   if (f32)
-    return launch_skinny<float, DecResidual<float>>(w, k, rows, z, k, n, k,
-                                                    {static_cast<const float *>(x), y, rows}, stream);
-  return launch_skinny<bf16_t, DecResidual<bf16_t>>(w, k, rows, z, k, n, k,
-                                                    {static_cast<const bf16_t *>(x), y, rows}, stream);
+    return launch_skinny<DecResidual<float>>(w, k, rows, z, k, n, k, {static_cast<const float *>(x), y, rows, nullptr, 0},
+                                             stream);
+  return launch_ring<DecResidual<bf16_t>, false>(
+      Operand{w, k}, rows, Operand{z, k}, n, k, splits,
+      {static_cast<const bf16_t *>(x), y, rows, extra, static_cast<int64_t>(n) * rows}, stream);
 }
 
 hipError_t decode_logits(bool f32, const void *w_out, int vocab, const void *z, int n, int h, float *part_m,
                          float *part_l, int32_t *part_arg, hipStream_t stream) {
   const DecLogits::Params ep{part_m, part_l, part_arg, n};
-  if (f32) return launch_skinny<float, DecLogits>(w_out, h, vocab, z, h, n, h, ep, stream);
-  return launch_skinny<bf16_t, DecLogits>(w_out, h, vocab, z, h, n, h, ep, stream);
+  if (f32) return launch_skinny<DecLogits>(w_out, h, vocab, z, h, n, h, ep, stream);
+  return launch_ring<DecLogits, false>(Operand{w_out, h}, vocab, Operand{z, h}, n, h, 1, ep, stream);
 }
 
 hipError_t decode_decide(const float *part_m, const float *part_l, const int32_t *part_arg, int tiles, int n,

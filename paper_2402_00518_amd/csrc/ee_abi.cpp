@@ -483,6 +483,7 @@ ee_status check_aliasing(int n_exits, const ee_exit *exits, const void *const *h
 struct DecLayout {
   size_t z = 0, u = 0, hg = 0, act = 0, y = 0, pm = 0, pl = 0, pa = 0, total = 0;
   int tiles = 0;
+  int slices = 1;  // of the down projection's K
 };
 
 DecLayout dec_layout(const ee_exit &e, int64_t n) {
@@ -498,16 +499,23 @@ DecLayout dec_layout(const ee_exit &e, int64_t n) {
   };
   L.z = take(N * h * es);
   if (e.kind == EE_EXIT_MLP) {
-    L.u = take(N * h * es);
-    L.hg = take(N * I * es);
     L.act = take(N * I * es);
     L.y = take(N * h * 4);
+    L.u = take(N * h * es);
+    L.hg = take(N * I * es);
   }
   L.tiles = ee::decode_tiles(static_cast<int>(e.vocab));
   L.pm = take(static_cast<size_t>(L.tiles) * N * 4);
   L.pl = take(static_cast<size_t>(L.tiles) * N * 4);
   L.pa = take(static_cast<size_t>(L.tiles) * N * 4);
   L.total = off;
+  if (e.kind == EE_EXIT_MLP) {
+    // The down projection runs when u, hg and the softmax partials hold
+    // nothing (u and hg have been read, the partials come later): its
+    // further slices of a split K go there.
+    L.slices = ee::decode_residual_splits(e.dtype == EE_F32, static_cast<int>(h), static_cast<int>(n), static_cast<int>(I),
+                                          1 + static_cast<int>((L.total - L.u) / (N * h * 4)));
+  }
   return L;
 }
 
@@ -588,13 +596,13 @@ ee_status run_decide(const ee_exit &e, const void *x, int64_t n64, float thresho
   if (e.kind == EE_EXIT_MLP) {
     EE_LAUNCH("decode mlp pre-norm", s,
               ee::launch_row_norm(f32, f32, x, n, h, e.rms_eps, e.gamma_mlp, nullptr, false, at(ws, L.u), s));
-    EE_LAUNCH("decode gate projection", s, ee::decode_store(f32, e.w_gate, I, at(ws, L.u), n, h, at(ws, L.hg), s));
-    EE_LAUNCH("decode up projection + swiglu", s,
-              ee::decode_swiglu(f32, e.w_up, I, at(ws, L.u), n, h, at(ws, L.hg), at(ws, L.act), s));
+    EE_LAUNCH("decode gate and up projections + swiglu", s,
+              ee::decode_gate_up(f32, e.w_gate, e.w_up, I, at(ws, L.u), n, h, at(ws, L.hg), at(ws, L.act), s));
     EE_LAUNCH("decode down projection + residual", s,
-              ee::decode_residual(f32, e.w_down, h, at(ws, L.act), n, I, x, atf(ws, L.y), s));
+              ee::decode_residual(f32, e.w_down, h, at(ws, L.act), n, I, x, atf(ws, L.y), L.slices, atf(ws, L.u), s));
     EE_LAUNCH("decode exit norm", s,
-              ee::launch_row_norm(true, f32, atf(ws, L.y), n, h, e.rms_eps, e.gamma, nullptr, false, at(ws, L.z), s));
+              ee::launch_row_norm(true, f32, atf(ws, L.y), n, h, e.rms_eps, e.gamma, nullptr, false, at(ws, L.z), s,
+                                  atf(ws, L.u), L.slices - 1));
     z = at(ws, L.z);
   } else if (e.kind == EE_EXIT_NORM) {
     EE_LAUNCH("decode exit norm", s,

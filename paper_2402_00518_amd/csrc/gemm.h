@@ -25,16 +25,12 @@
 #pragma once
 
 #include <algorithm>
+#include <cstdlib>
 
 #include "ee_device.h"
+#include "ring.h"
 
 namespace ee {
-
-struct Operand {
-  const void *ptr;
-  int64_t ld;         // elements between consecutive rows of the stored matrix
-  int64_t pair = 0;   // interleaved pair (KMajorPairLoader): bytes from the first matrix to the second
-};
 
 struct GemmShape {
   int M, N, K;
@@ -46,7 +42,7 @@ constexpr int kNumXcd = 8;
 constexpr int kGroupM = 4;
 constexpr int kLoopBlocks = 256;  // grid of the looping kernels: one block per CU of a 256-CU GPU (a multiple of kNumXcd)
 
-template <int BM_, int BN_, int WM_, int WN_, int MIN_BLOCKS_>
+template <int BM_, int BN_, int WM_, int WN_, int MIN_BLOCKS_, int STAGES_ = 2>
 struct TileCfg {
   static constexpr int BM = BM_, BN = BN_, WM = WM_, WN = WN_;
   static constexpr int MIN_BLOCKS = MIN_BLOCKS_;  // workgroups per CU the registers must allow
@@ -54,6 +50,8 @@ struct TileCfg {
   static constexpr int THREADS = WAVES_M * WAVES_N * 64;
   static constexpr int MB = WM / 32, NB = WN / 32;
   static constexpr int STAGE_BYTES = (BM + BN) * kRowBytes;
+  static constexpr int STAGES = STAGES_;  // LDS stages
+  static constexpr int SMEM_BYTES = STAGES * STAGE_BYTES;
 };
 // 128 x 128 tile, 64 x 64 per wave: every fp32 GEMM.
 using CfgSmall = TileCfg<128, 128, 64, 64, 2>;
@@ -61,6 +59,9 @@ using CfgSmall = TileCfg<128, 128, 64, 64, 2>;
 // 1.5x the MFMA work per byte read from LDS of the small tile, and a second
 // wave per SIMD to issue while the other waits.
 using CfgBig = TileCfg<256, 256, 128, 64, 1>;
+// 128 x 128 tile, 64 x 64 per wave, a ring of 4 stages: bf16 products with too
+// few 256 x 256 tiles to fill the chip.
+using CfgMid = TileCfg<128, 128, 64, 64, 1, 4>;
 
 template <typename T> struct Elem;
 template <> struct Elem<bf16_t> {
@@ -444,38 +445,6 @@ static __device__ __forceinline__ void run(const Operand &A, const Operand &B, c
 };
 
 // ------------------------------------------------------------ bf16 main loop
-// 16 bytes a lane from base + off (off per lane) to LDS: lane l's bytes land
-// at lds + 16 l.  The compiler does not count these loads: whoever reads what
-// they bring waits with wait_vm, and a barrier makes it visible to the block.
-// (Only inputs, so nothing of the load in flight sits in a register.)
-__device__ __forceinline__ void load_lds16(const char *base, uint32_t off, uint32_t lds) {
-  // base and lds are the same in every lane; say so, as the asm takes them in scalar registers
-  const uint64_t b = reinterpret_cast<uint64_t>(base);
-  base = reinterpret_cast<const char *>(
-      static_cast<uint64_t>(static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(b)))) |
-      static_cast<uint64_t>(static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(b >> 32)))) << 32);
-  lds = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(lds)));
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(off), "s"(base)
-               : "memory");
-}
-template <int N> __device__ __forceinline__ void wait_vm() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
-__device__ __forceinline__ void wait_lgkm() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
-// A barrier without a wait for loads in flight (as __syncthreads would have).
-__device__ __forceinline__ void phase_barrier() {
-  __builtin_amdgcn_sched_barrier(0);
-  asm volatile("s_barrier" ::: "memory");
-  __builtin_amdgcn_sched_barrier(0);
-}
-
-typedef short s16x4_t __attribute__((ext_vector_type(4)));
-typedef __attribute__((address_space(3))) s16x4_t lds_s16x4_t;
-
-// Accumulator rows of a 16 x 16 MFMA block: lanes 16 g .. 16 g + 15 hold rows
-// 4 g .. 4 g + 3 of the block, which stand for rows 0, 8, 4, 12 (+ 0..3) of
-// the tile's 16, so that one lane swap per register pair turns two column
-// blocks into the 32 x 32 layout of TileCtx.
-__device__ __forceinline__ int acc_row(int r) { return ((r >> 2) & 1) * 8 + ((r >> 3) & 1) * 4 + (r & 3); }
-
 // One operand of a 256-row tile, in two halves of 128 rows.  Half q holds,
 // for each wave that owns rows of this operand, the wave's 16-row blocks q *
 // WR / 2 .. : WR rows a wave (128 for A, 64 for B), WR / 2 of them per half.
@@ -607,7 +576,7 @@ struct TileOperandB16 {
 // reached 1340 (12, 4, 8 and no fragment reads a phase: 1525; with a raised
 // wave priority around the MFMAs: 1530).
 template <bool AK, bool BKM, class Epi, class Cfg, bool LOOP>
-struct GemmBlock<bf16_t, AK, BKM, Epi, Cfg, LOOP> {
+struct GemmBlockBig {
   static __device__ __forceinline__ void run(const Operand &A, const Operand &B, const GemmShape &s,
                                              const typename Epi::Params &ep, int b, int nblk, int kz, char *smem) {
     static_assert(Cfg::BM == 256 && Cfg::BN == 256 && Cfg::WM == 128 && Cfg::WN == 64, "8 waves of 128 x 64");
@@ -726,25 +695,39 @@ struct GemmBlock<bf16_t, AK, BKM, Epi, Cfg, LOOP> {
     if (wave_m == 0) phase_barrier();
     wait_vm<0>();  // the epilogue's first barrier then frees the tile's LDS
 
-    // Two 16-column blocks side by side -> the 32 x 32 layout: the swap hands
-    // lanes 16..31 (48..63) the right block's columns of the rows that lanes
-    // 0..15 (32..47) keep of the left one, and the other way round.
     f32x16_t blk[Cfg::MB][Cfg::NB];
-    static_for<8>([&](auto i) EE_ALWAYS_INLINE {
-      static_for<2>([&](auto j) EE_ALWAYS_INLINE {
-        static_for<4>([&](auto e) EE_ALWAYS_INLINE {
-          constexpr int I = decltype(i)::value, J = decltype(j)::value, E = decltype(e)::value;
-          const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(acc[I][2 * J][E]),
-                                                          __float_as_uint(acc[I][2 * J + 1][E]), false, false);
-          blk[I / 2][J][(I % 2) * 8 + E] = __uint_as_float(r[0]);
-          blk[I / 2][J][(I % 2) * 8 + 4 + E] = __uint_as_float(r[1]);
-        });
-      });
-    });
+    to_blocks32<Cfg::MB, Cfg::NB>(acc, blk);
     TileCtx<Cfg> ctx{s.M, s.N, m0, n0, tile_m, tile_n, wave_m, wave_n, lane, smem, kz};
     Epi::template apply<Cfg>(ep, blk, ctx);
   }
 };
+
+// bf16 on the small tile.
+template <bool AK, bool BKM, class Epi, class Cfg, bool LOOP>
+struct GemmBlockMid {
+  static __device__ __forceinline__ void run(const Operand &A, const Operand &B, const GemmShape &s,
+                                             const typename Epi::Params &ep, int b, int nblk, int kz, char *smem) {
+    using R = Ring<Cfg::BM, Cfg::BN, Cfg::WM, Cfg::WN, Cfg::STAGES, AK, BKM, false, EpiPairB<Epi>::value>;
+    int tid_v = threadIdx.x;
+    if constexpr (LOOP) asm volatile("" : "+v"(tid_v));
+    const int tid = tid_v, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    int tile_m, tile_n;
+    tile_of_block(b, nblk, cdiv(s.M, Cfg::BM), cdiv(s.N, Cfg::BN), tile_m, tile_n);
+    const int m0 = tile_m * Cfg::BM, n0 = tile_n * Cfg::BN;
+    const int kbeg = s.kchunk > 0 ? kz * s.kchunk : 0;
+    const int K = (s.kchunk > 0 ? min(s.K, kbeg + s.kchunk) : s.K) - kbeg;
+    f32x4_t acc[2 * Cfg::MB][2 * Cfg::NB];
+    R::run(A, m0, s.M, B, n0, s.N, kbeg, K, tid, smem, acc);
+    f32x16_t blk[Cfg::MB][Cfg::NB];
+    to_blocks32<Cfg::MB, Cfg::NB>(acc, blk);
+    TileCtx<Cfg> ctx{s.M, s.N, m0, n0, tile_m, tile_n, wave / Cfg::WAVES_N, wave % Cfg::WAVES_N, lane, smem, kz};
+    Epi::template apply<Cfg>(ep, blk, ctx);
+  }
+};
+
+template <bool AK, bool BKM, class Epi, class Cfg, bool LOOP>
+struct GemmBlock<bf16_t, AK, BKM, Epi, Cfg, LOOP>
+    : std::conditional_t<Cfg::BM == 256, GemmBlockBig<AK, BKM, Epi, Cfg, LOOP>, GemmBlockMid<AK, BKM, Epi, Cfg, LOOP>> {};
 
 template <typename T, bool AK, bool BKM, class Epi, class Cfg, bool LOOP = false>
 __device__ __forceinline__ void gemm_block(const Operand &A, const Operand &B, const GemmShape &s,
@@ -755,7 +738,7 @@ __device__ __forceinline__ void gemm_block(const Operand &A, const Operand &B, c
 template <typename T, bool AK, bool BKM, class Epi, class Cfg>
 __global__ __launch_bounds__(Cfg::THREADS, Cfg::MIN_BLOCKS) void gemm_kernel(Operand A, Operand B, GemmShape s,
                                                                 typename Epi::Params ep) {
-  __shared__ __attribute__((aligned(16))) char smem[2 * Cfg::STAGE_BYTES];
+  __shared__ __attribute__((aligned(16))) char smem[Cfg::SMEM_BYTES];
   gemm_block<T, AK, BKM, Epi, Cfg>(A, B, s, ep, blockIdx.x, gridDim.x, blockIdx.z, smem);
 }
 
@@ -768,7 +751,7 @@ __global__ __launch_bounds__(Cfg::THREADS, Cfg::MIN_BLOCKS) void gemm_kernel(Ope
 template <typename T, bool AK, bool BKM, class Epi, class Cfg>
 __global__ __launch_bounds__(Cfg::THREADS, Cfg::MIN_BLOCKS) void gemm_gated_kernel(Operand A, Operand B, GemmShape s,
                                                                       typename Epi::Params ep, const int *run_if) {
-  __shared__ __attribute__((aligned(16))) char smem[2 * Cfg::STAGE_BYTES];
+  __shared__ __attribute__((aligned(16))) char smem[Cfg::SMEM_BYTES];
   if (*run_if == 0) return;  // the same word for every thread
   const int tiles = cdiv(s.M, Cfg::BM) * cdiv(s.N, Cfg::BN);
   for (int t = blockIdx.x; t < tiles; t += gridDim.x) {
@@ -787,7 +770,7 @@ template <typename T, bool AK, bool BKM, class Epi, class Cfg>
 __global__ __launch_bounds__(Cfg::THREADS, Cfg::MIN_BLOCKS) void gemm_persistent_kernel(Operand A, Operand B,
                                                                            GemmShape s,
                                                                            typename Epi::Params ep) {
-  __shared__ __attribute__((aligned(16))) char smem[2 * Cfg::STAGE_BYTES];
+  __shared__ __attribute__((aligned(16))) char smem[Cfg::SMEM_BYTES];
   const int tiles = cdiv(s.M, Cfg::BM) * cdiv(s.N, Cfg::BN);
   for (int t = blockIdx.x; t < tiles; t += gridDim.x) {
     gemm_block<T, AK, BKM, Epi, Cfg, true>(A, B, s, ep, t, tiles, 0, smem);
@@ -806,7 +789,7 @@ template <typename T, bool AK1, bool BKM1, class Epi1, bool AK2, bool BKM2, clas
 __global__ __launch_bounds__(Cfg::THREADS, Cfg::MIN_BLOCKS) void gemm_pair_kernel(
     Operand A1, Operand B1, GemmShape s1, typename Epi1::Params ep1, Operand A2, Operand B2, GemmShape s2,
     typename Epi2::Params ep2, int blocks1, int base2) {
-  __shared__ __attribute__((aligned(16))) char smem[2 * Cfg::STAGE_BYTES];
+  __shared__ __attribute__((aligned(16))) char smem[Cfg::SMEM_BYTES];
   const int b = blockIdx.x;
   if (b < blocks1)
     gemm_block<T, AK1, BKM1, Epi1, Cfg>(A1, B1, s1, ep1, b, blocks1, 0, smem);
@@ -823,7 +806,7 @@ template <typename T, bool AK1, bool BKM1, class Epi1, bool AK2, bool BKM2, clas
 __global__ __launch_bounds__(Cfg::THREADS, Cfg::MIN_BLOCKS) void gemm_pair_persistent_kernel(
     Operand A1, Operand B1, GemmShape s1, typename Epi1::Params ep1, Operand A2, Operand B2, GemmShape s2,
     typename Epi2::Params ep2, int blocks1, int base2, int total) {
-  __shared__ __attribute__((aligned(16))) char smem[2 * Cfg::STAGE_BYTES];
+  __shared__ __attribute__((aligned(16))) char smem[Cfg::SMEM_BYTES];
   const int tiles2 = cdiv(s2.M, Cfg::BM) * cdiv(s2.N, Cfg::BN);
   for (int t = blockIdx.x; t < total; t += gridDim.x) {
     if (t < blocks1) {
@@ -914,14 +897,24 @@ hipError_t launch_gemm_pair(Operand A1, Operand B1, GemmShape s1, const typename
   return hipGetLastError();
 }
 
-// bf16 GEMMs take the 256 x 256 tile (either operand K-major or MN-major),
-// fp32 GEMMs the 128 x 128 tile.
+// bf16 GEMMs take the 256 x 256 tile, or the 128 x 128 tile where that shortens
+// the launch (use_mid_tile); fp32 GEMMs the 128 x 128 tile.
+inline bool use_mid_tile(int64_t big_tiles, int64_t mid_tiles) {
+  static const char *e = getenv("EE_MID");
+  return e ? atoi(e) * big_tiles <= 100 * kLoopBlocks : false;
+}
+inline bool use_mid_tile(const GemmShape &s) {
+  return use_mid_tile(static_cast<int64_t>(cdiv(s.M, 256)) * cdiv(s.N, 256), static_cast<int64_t>(cdiv(s.M, 128)) * cdiv(s.N, 128));
+}
 template <typename T, bool AK, bool BKM, class Epi>
 hipError_t run_gemm(Operand A, Operand B, GemmShape s, const typename Epi::Params &ep, hipStream_t stream) {
-  if constexpr (std::is_same<T, bf16_t>::value)
+  if constexpr (std::is_same<T, bf16_t>::value) {
+    if (use_mid_tile(s)) return launch_gemm<T, AK, BKM, Epi, CfgMid>(A, B, s, ep, stream);
     return launch_gemm<T, AK, BKM, Epi, CfgBig>(A, B, s, ep, stream);
-  else
+  }
+  else {
     return launch_gemm<T, AK, BKM, Epi, CfgSmall>(A, B, s, ep, stream);
+  }
 }
 
 template <typename T, bool AK1, bool BKM1, class Epi1, bool AK2, bool BKM2, class Epi2>

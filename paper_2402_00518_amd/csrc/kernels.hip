@@ -160,53 +160,96 @@ __global__ __launch_bounds__(256) void row_rms_split_kernel(float *x, int n, int
 
 // Statistics and application of the exit norm in one launch, one block per
 // row, for the few rows of a decode call: z = (x - mu) r * gain (+ bias),
-// mu = 0 unless `centre` (LayerNorm), r from the centred second moment.  The
-// row is read again for each pass (from L1/L2).  h a multiple of 4.
-template <typename Tin, typename T>
+// mu = 0 unless `centre` (LayerNorm), r from the centred second moment.  h a
+// multiple of 8.  A latency chain of one block, so rows of up to IT * 2048
+// values stay in registers, with the gain and the bias, all loaded at once
+// (longer rows, IT = 0, are read again for each pass).  n_extra: x (fp32) is
+// the first of several slices of a split product, gridDim.x rows of h apart
+// from `extra` on, added in order.
+template <typename Tin, typename T, int IT>
 __global__ __launch_bounds__(256) void row_norm_kernel(const Tin *x, int h, float eps, const T *gain, const T *bias,
-                                                       int centre, T *z) {
-  __shared__ float red[4];
+                                                       int centre, T *z, const float *extra, int n_extra) {
+  __shared__ float red[2][4];
   const int tid = threadIdx.x;
-  const Tin *xr = x + static_cast<int64_t>(blockIdx.x) * h;
-  auto block_sum = [&](float v) {
-    v = warp_sum(v);
-    if ((tid & 63) == 0) red[tid >> 6] = v;
+  const int64_t row = static_cast<int64_t>(blockIdx.x) * h, zs = static_cast<int64_t>(gridDim.x) * h;
+  auto load_x = [&](int j, float (&v)[8]) EE_ALWAYS_INLINE {
+    load_f32<8>(x + row + j, v);
+    if constexpr (std::is_same<Tin, float>::value) {
+      for (int q = 0; q < n_extra; ++q) {
+        float t[8];
+        load_f32<8>(extra + q * zs + row + j, t);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] += t[e];
+      }
+    }
+  };
+  constexpr int KEEP = IT > 0 ? IT : 1;
+  float v[KEEP][8], g[KEEP][8], b[KEEP][8];
+  auto load_gain = [&](int j, int c) EE_ALWAYS_INLINE {
+    load_f32<8>(gain + j, g[c]);
+    if (bias != nullptr) {
+      load_f32<8>(bias + j, b[c]);
+    } else {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) b[c][e] = 0.0f;
+    }
+  };
+  if constexpr (IT > 0) {
+#pragma unroll
+    for (int c = 0; c < IT; ++c) {
+      const int j = (c * 256 + tid) * 8;
+      if (j < h) {
+        load_x(j, v[c]);
+        load_gain(j, c);
+      }
+    }
+  }
+  // f(column, row values, slot of the gain) for each 8 values of the thread
+  auto each = [&](auto &&f) EE_ALWAYS_INLINE {
+    if constexpr (IT > 0) {
+#pragma unroll
+      for (int c = 0; c < IT; ++c) {
+        const int j = (c * 256 + tid) * 8;
+        if (j < h) f(j, v[c], c);
+      }
+    } else {
+      for (int j = tid * 8; j < h; j += 2048) {
+        load_x(j, v[0]);
+        f(j, v[0], 0);
+      }
+    }
+  };
+  auto block_sum = [&](float s, int slot) EE_ALWAYS_INLINE {
+    s = warp_sum(s);
+    if ((tid & 63) == 0) red[slot][tid >> 6] = s;
     __syncthreads();
-    const float t = (red[0] + red[1]) + (red[2] + red[3]);
-    __syncthreads();
-    return t;
+    return (red[slot][0] + red[slot][1]) + (red[slot][2] + red[slot][3]);
   };
   float mean = 0.0f;
   if (centre) {
     float t = 0.0f;
-    for (int j = tid * 4; j < h; j += 1024) {
-      float v[4];
-      load_f32<4>(xr + j, v);
-      t += (v[0] + v[1]) + (v[2] + v[3]);
-    }
-    mean = block_sum(t) / static_cast<float>(h);
+    each([&](int, const float (&w)[8], int) EE_ALWAYS_INLINE {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) t += w[e];
+    });
+    mean = block_sum(t, 0) / static_cast<float>(h);
   }
   float s = 0.0f;
-  for (int j = tid * 4; j < h; j += 1024) {
-    float v[4];
-    load_f32<4>(xr + j, v);
+  each([&](int, const float (&w)[8], int) EE_ALWAYS_INLINE {
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const float c = v[e] - mean;
+    for (int e = 0; e < 8; ++e) {
+      const float c = w[e] - mean;
       s += c * c;
     }
-  }
-  const float r = 1.0f / sqrtf(block_sum(s) / static_cast<float>(h) + eps);
-  T *zr = z + static_cast<int64_t>(blockIdx.x) * h;
-  for (int j = tid * 4; j < h; j += 1024) {
-    float v[4], g[4], b[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-    load_f32<4>(xr + j, v);
-    load_f32<4>(gain + j, g);
-    if (bias != nullptr) load_f32<4>(bias + j, b);
+  });
+  const float r = 1.0f / sqrtf(block_sum(s, 1) / static_cast<float>(h) + eps);
+  each([&](int j, const float (&w)[8], int c) EE_ALWAYS_INLINE {
+    if constexpr (IT == 0) load_gain(j, 0);
+    float o[8];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) v[e] = (v[e] - mean) * r * g[e] + b[e];
-    store4(zr + j, f32x4_t{v[0], v[1], v[2], v[3]});
-  }
+    for (int e = 0; e < 8; ++e) o[e] = (w[e] - mean) * r * g[c][e] + b[c][e];
+    store_f32<8>(z + row + j, o);
+  });
 }
 
 // 64 tokens x 64 features per block.  Row-major outputs are written
@@ -837,19 +880,32 @@ hipError_t launch_row_rms_split(float *x, int n, int h, float eps, float *r, Spl
 }
 
 hipError_t launch_row_norm(bool x_f32, bool f32, const void *x, int n, int h, float eps, const void *gain,
-                           const void *bias, bool centre, void *z, hipStream_t stream) {
+                           const void *bias, bool centre, void *z, hipStream_t stream, const float *extra,
+                           int n_extra) {
   if (n <= 0) return hipSuccess;
-  if (h % 4 != 0 || gain == nullptr) return hipErrorInvalidValue;
+  if (h % 8 != 0 || gain == nullptr || (n_extra > 0 && (!x_f32 || extra == nullptr))) return hipErrorInvalidValue;
   const dim3 grid(static_cast<unsigned>(n));
   const int c = centre ? 1 : 0;
   EE_DISPATCH(f32, {
     const T *g = static_cast<const T *>(gain), *b = static_cast<const T *>(bias);
-    if (x_f32)
-      hipLaunchKernelGGL((row_norm_kernel<float, T>), grid, dim3(256), 0, stream, static_cast<const float *>(x), h, eps,
-                         g, b, c, static_cast<T *>(z));
+    T *zt = static_cast<T *>(z);
+    auto go = [&](auto it) {
+      constexpr int IT = decltype(it)::value;
+      if (x_f32)
+        hipLaunchKernelGGL((row_norm_kernel<float, T, IT>), grid, dim3(256), 0, stream, static_cast<const float *>(x), h,
+                           eps, g, b, c, zt, extra, n_extra);
+      else
+        hipLaunchKernelGGL((row_norm_kernel<bf16_t, T, IT>), grid, dim3(256), 0, stream, static_cast<const bf16_t *>(x),
+                           h, eps, g, b, c, zt, extra, 0);
+    };
+    if (h <= 2048)
+      go(std::integral_constant<int, 1>{});
+    else if (h <= 4096)
+      go(std::integral_constant<int, 2>{});
+    else if (h <= 8192)
+      go(std::integral_constant<int, 4>{});
     else
-      hipLaunchKernelGGL((row_norm_kernel<bf16_t, T>), grid, dim3(256), 0, stream, static_cast<const bf16_t *>(x), h,
-                         eps, g, b, c, static_cast<T *>(z));
+      go(std::integral_constant<int, 0>{});
   });
   return hipGetLastError();
 }

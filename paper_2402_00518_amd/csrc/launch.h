@@ -60,9 +60,12 @@ hipError_t launch_norm_rows(bool f32, const void *x, int64_t ldx, int n, int ldn
 
 // The exit norm of a few rows in one launch (decode): z[n][h] = (x - mu) r *
 // gain (+ bias), with mu the row mean when `centre` (LayerNorm), else 0, and
-// r = (mean (x - mu)^2 + eps)^(-1/2).  x is fp32 when x_f32, z is `f32`.
+// r = (mean (x - mu)^2 + eps)^(-1/2).  x is fp32 when x_f32, z is `f32`.  With
+// extra (fp32 x): x stands for the sum, in order, of itself and `n_extra`
+// partial sums [n][h].
 hipError_t launch_row_norm(bool x_f32, bool f32, const void *x, int n, int h, float eps, const void *gain,
-                           const void *bias, bool centre, void *z, hipStream_t stream);
+                           const void *bias, bool centre, void *z, hipStream_t stream, const float *extra = nullptr,
+                           int n_extra = 0);
 
 // Combine the per-tile softmax partials of each token into LSE, the row NLL
 // and the loss weight s_n.  Also flags targets outside [0, V).
@@ -209,15 +212,19 @@ struct AdamBatchArgs {
 };
 // ---------------------------------------------------------------- decode
 // Skinny products of the decode-time exit head (decode.hip): n token rows
-// (any n; 32 per pass) against a weight of `rows` K-contiguous rows, K a
+// (any n) against a weight of `rows` K-contiguous rows, K a
 // multiple of 64.  Outputs are token-major, [n][rows].
 int decode_tiles(int rows);  // partial rows per token of decode_logits
-hipError_t decode_store(bool f32, const void *w, int rows, const void *z, int n, int k, void *out,
-                        hipStream_t stream);
-hipError_t decode_swiglu(bool f32, const void *w, int rows, const void *z, int n, int k, const void *hg,
-                         void *act, hipStream_t stream);
+// Gate and up projections with the SwiGLU product, act[n][rows] (fp32: two
+// launches, the gate's product through hg[n][rows]; bf16: one, hg unused).
+hipError_t decode_gate_up(bool f32, const void *w_gate, const void *w_up, int rows, const void *z, int n, int k,
+                          void *hg, void *act, hipStream_t stream);
+// Y = X + C, with K in `splits` slices (at most `most`: see
+// decode_residual_splits): slice 0 adds X, slice z > 0 leaves its partial sums
+// [n][rows] at extra + (z - 1) n rows, for launch_row_norm to add.
+int decode_residual_splits(bool f32, int rows, int n, int k, int most);
 hipError_t decode_residual(bool f32, const void *w, int rows, const void *z, int n, int k, const void *x,
-                           float *y, hipStream_t stream);
+                           float *y, int splits, float *extra, hipStream_t stream);
 // Softmax partials of S = Z W_out^T: [decode_tiles(vocab)][n] max, sum exp, lowest argmax.
 hipError_t decode_logits(bool f32, const void *w_out, int vocab, const void *z, int n, int h, float *part_m,
                          float *part_l, int32_t *part_arg, hipStream_t stream);

@@ -1,0 +1,274 @@
+// Building blocks of the bf16 products on v_mfma_f32_16x16x32_bf16 whose operands
+// go straight from memory into LDS, and the ring main loop that small tiles
+// and the decode-time products share.
+#pragma once
+
+#include "ee_device.h"
+
+namespace ee {
+
+struct Operand {
+  const void *ptr;
+  int64_t ld;         // elements between consecutive rows of the stored matrix
+  int64_t pair = 0;   // interleaved pair of matrices: bytes from the first matrix to the second
+};
+
+// 16 bytes a lane from base + off (off per lane) to LDS: lane l's bytes land
+// at lds + 16 l.  The compiler does not count these loads: whoever reads what
+// they bring waits with wait_vm, and a barrier makes it visible to the block.
+// (Only inputs, so nothing of the load in flight sits in a register.)
+__device__ __forceinline__ void load_lds16(const char *base, uint32_t off, uint32_t lds) {
+  // base and lds are the same in every lane; say so, as the asm takes them in scalar registers
+  const uint64_t b = reinterpret_cast<uint64_t>(base);
+  base = reinterpret_cast<const char *>(
+      static_cast<uint64_t>(static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(b)))) |
+      static_cast<uint64_t>(static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(b >> 32)))) << 32);
+  lds = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(lds)));
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(off), "s"(base)
+               : "memory");
+}
+template <int N> __device__ __forceinline__ void wait_vm() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
+__device__ __forceinline__ void wait_lgkm() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
+// A barrier without a wait for loads in flight (as __syncthreads would have).
+__device__ __forceinline__ void phase_barrier() {
+  __builtin_amdgcn_sched_barrier(0);
+  asm volatile("s_barrier" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
+}
+
+typedef short s16x4_t __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) s16x4_t lds_s16x4_t;
+
+// Accumulator rows of a 16 x 16 MFMA block: lanes 16 g .. 16 g + 15 hold rows
+// 4 g .. 4 g + 3 of the block, which stand for rows 0, 8, 4, 12 (+ 0..3) of
+// the tile's 16, so that one lane swap per register pair turns two column
+// blocks into the 32 x 32 layout of TileCtx.
+__device__ __forceinline__ int acc_row(int r) { return ((r >> 2) & 1) * 8 + ((r >> 3) & 1) * 4 + (r & 3); }
+
+// Two 16-column blocks side by side -> the 32 x 32 layout: the swap hands
+// lanes 16..31 (48..63) the right block's columns of the rows that lanes 0..15
+// (32..47) keep of the left one, and the other way round.
+template <int MB, int NB>
+__device__ __forceinline__ void to_blocks32(const f32x4_t (&acc)[2 * MB][2 * NB], f32x16_t (&blk)[MB][NB]) {
+  static_for<2 * MB>([&](auto i) EE_ALWAYS_INLINE {
+    static_for<NB>([&](auto j) EE_ALWAYS_INLINE {
+      static_for<4>([&](auto e) EE_ALWAYS_INLINE {
+        constexpr int I = decltype(i)::value, J = decltype(j)::value, E = decltype(e)::value;
+        const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(acc[I][2 * J][E]),
+                                                        __float_as_uint(acc[I][2 * J + 1][E]), false, false);
+        blk[I / 2][J][(I % 2) * 8 + E] = __uint_as_float(r[0]);
+        blk[I / 2][J][(I % 2) * 8 + 4 + E] = __uint_as_float(r[1]);
+      });
+    });
+  });
+}
+
+// One operand of a ring stage: ROWS rows by 64 values of K, loaded by THREADS
+// threads, 16 bytes each a load.
+// K-major: LDS rows of 128 bytes, 16-byte chunk c of row r at c ^ ((r / 2) mod
+// 8); PAIR: rows of two matrices of F rows each in alternating blocks of 32,
+// tile row r being row (r / 64) * 32 + r % 32 of the first matrix when (r / 32)
+// is even, else of the second (row0 and rows count the interleaved rows).
+// MN-major (128 rows): 64 k-rows of 256 bytes, chunk c of k-row k at c ^ (2 (k
+// mod 4) + 8 (k / 8 mod 2)), read with ds_read_b64_tr_b16: it gives lane 4 a + b
+// of each 16-lane group element b of the 8-byte pieces that lanes a, a + 4,
+// a + 8, a + 12 of the group address.
+template <bool KM, int ROWS, int THREADS, bool PERM, bool PAIR>
+struct RingOperand {
+  static constexpr int LOADS = ROWS * 8 / THREADS;
+  static constexpr int BYTES = ROWS * 128;
+  static_assert(LOADS * THREADS == ROWS * 8, "every thread loads the same number of chunks");
+  static_assert(KM || (ROWS == 128 && !PAIR), "MN-major k-rows are 256 bytes");
+  static_assert(!PAIR || THREADS / 8 <= 32, "a load's rows come from one matrix");
+  uint32_t off[LOADS];
+  uint32_t ld2, kr;  // MN-major: bytes per k-row; k-row of the thread's first chunk
+  const char *rd[KM ? 2 : ROWS / 16];
+  const char *base;
+  int64_t pair, step;
+
+  __device__ __forceinline__ static int swz(int k) { return 2 * (k & 3) + 8 * ((k >> 3) & 1); }
+
+  // row0: first (interleaved) row of the tile, rows: rows of the operand;
+  // wrow: the wave's first row in the tile; lds: the operand's LDS in stage 0.
+  __device__ __forceinline__ void init(const Operand &O, int row0, int rows, int kbeg, int tid, int wrow, int lane,
+                                       const char *lds) {
+    const bf16_t *p = static_cast<const bf16_t *>(O.ptr);
+    ld2 = static_cast<uint32_t>(O.ld * 2);
+    pair = O.pair;
+    if constexpr (KM) {
+      const int r0 = PAIR ? row0 / 2 : row0, last = (PAIR ? rows / 2 : rows) - 1;
+      base = reinterpret_cast<const char *>(p + static_cast<int64_t>(r0) * O.ld + kbeg);
+      step = 128;
+      static_for<LOADS>([&](auto e) EE_ALWAYS_INLINE {
+        const int c = decltype(e)::value * THREADS + tid, lr = c >> 3, ch = (c & 7) ^ ((lr >> 1) & 7);
+        const int r = PAIR ? (lr >> 6) * 32 + (lr & 31) : lr;
+        off[e] = static_cast<uint32_t>(min(r0 + r, last) - r0) * ld2 + ch * 16;
+      });
+      const int r = PERM ? acc_row(lane & 15) : lane & 15, x = (r >> 1) & 7;
+      static_for<2>([&](auto ks) EE_ALWAYS_INLINE {
+        rd[ks] = lds + (wrow + r) * 128 + (((decltype(ks)::value * 4 + (lane >> 4)) ^ x) << 4);
+      });
+    } else {
+      base = reinterpret_cast<const char *>(p + static_cast<int64_t>(kbeg) * O.ld + row0);
+      step = static_cast<int64_t>(ld2) * 64;
+      kr = tid >> 4;
+      static_for<LOADS>([&](auto e) EE_ALWAYS_INLINE {
+        const int c = decltype(e)::value * THREADS + tid, k = c >> 4, ch = (c & 15) ^ swz(k);
+        off[e] = static_cast<uint32_t>(min(row0 + ch * 8, rows - 8) - row0) * 2;
+      });
+      const int k = 8 * (lane >> 4) + ((lane >> 2) & 3), j = lane & 3;
+      const int m = PERM ? (j & 1) * 8 + (j >> 1) * 4 : 4 * j;
+      static_for<ROWS / 16>([&](auto i) EE_ALWAYS_INLINE {
+        const int row = (wrow + decltype(i)::value * 16 + m) & (ROWS - 1);  // (blocks past the wave's rows are not read)
+        rd[i] = lds + k * 256 + (((row >> 3) ^ swz(k)) << 4) + (row & 7) * 2;
+      });
+    }
+  }
+  // Stage t into LDS from lds_wave on (the wave's first chunk of the operand);
+  // left: values of K from this stage on (MN-major k-rows past them re-read the
+  // last one).
+  __device__ __forceinline__ void load(int t, int left, uint32_t lds_wave) const {
+    const char *p = base + static_cast<int64_t>(t) * step;
+    static_for<LOADS>([&](auto e) EE_ALWAYS_INLINE {
+      constexpr int E = decltype(e)::value;
+      uint32_t o = off[E];
+      if constexpr (!KM) o += __umul24(min(static_cast<int>(kr) + E * THREADS / 16, left - 1), ld2);
+      load_lds16(PAIR && ((E * THREADS / 8) >> 5) % 2 == 1 ? p + pair : p, o, lds_wave + E * THREADS * 16);
+    });
+  }
+  // Zero the chunks this thread loads whose k-rows lie past K (MN-major).
+  __device__ __forceinline__ void zero_tail(int left, int tid, char *lds) const {
+    static_for<LOADS>([&](auto e) EE_ALWAYS_INLINE {
+      constexpr int E = decltype(e)::value;
+      if (static_cast<int>(kr) + E * THREADS / 16 >= left)
+        *reinterpret_cast<u32x4_t *>(lds + E * THREADS * 16 + tid * 16) = u32x4_t{0, 0, 0, 0};
+    });
+  }
+  // Fragments of NBLK 16-row blocks at the KS-th 32 values of K of the stage
+  // `stage` bytes from stage 0.
+  template <int KS, int NBLK>
+  __device__ __forceinline__ void read(int stage, bf16x8_t (&f)[NBLK]) const {
+    static_for<NBLK>([&](auto i) EE_ALWAYS_INLINE {
+      constexpr int I = decltype(i)::value;
+      if constexpr (KM) {
+        f[I] = *reinterpret_cast<const bf16x8_t *>(rd[KS] + stage + I * 2048);
+      } else {
+        const char *p = rd[I] + stage + KS * 8192;
+        const s16x4_t both[2] = {__builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_t *)(p)),
+                                 __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_t *)(p + 1024))};
+        f[I] = __builtin_bit_cast(bf16x8_t, both);
+      }
+    });
+  }
+};
+
+// Ring of NS stages of 64 values of K: the stage NS - 1 further on is loaded
+// while one is consumed, one barrier per stage.  A BM x BN tile on waves of
+// WM x WN.  On return acc holds the wave's outputs, every load has landed and
+// every wave has read what it needs (a barrier was passed since).
+//
+// PARTS = 4: K is summed in four consecutive parts, (0 + 1) + (2 + 3), and the
+// tiles take them in different orders (0123, 1032, 2301, 3210).  Rows whose
+// stride is a power of two lie in the same few memory channels at one K, and
+// tiles that walk K in step all wait for those.  Every tile adds the same
+// values in the same order up to swapped summands, so equal rows still give
+// equal sums.
+template <int BM_, int BN_, int WM_, int WN_, int NS_, bool AK, bool BKM, bool A_PAIR, bool B_PAIR, int PARTS = 1>
+struct Ring {
+  static constexpr int BM = BM_, BN = BN_, WM = WM_, WN = WN_, NS = NS_;
+  static constexpr int WAVES_M = BM / WM, WAVES_N = BN / WN, THREADS = WAVES_M * WAVES_N * 64;
+  static constexpr int STAGE_BYTES = (BM + BN) * 128;
+  using TA = RingOperand<AK, BM, THREADS, true, A_PAIR>;
+  using TB = RingOperand<BKM, BN, THREADS, false, B_PAIR>;
+  static constexpr int LOADS = TA::LOADS + TB::LOADS;
+  using Acc = f32x4_t[WM / 16][WN / 16];
+  static_assert((NS - 2) * LOADS <= 63, "loads in flight past the waited-for stage");
+  static_assert(PARTS == 1 || ((PARTS == 4 || PARTS == 8) && AK), "parts: 1, or 4 or 8 of a K-major product");
+
+  template <class F> __device__ __forceinline__ static void each(F &&f) {
+    static_for<WM / 16>([&](auto i) EE_ALWAYS_INLINE {
+      static_for<WN / 16>([&](auto j) EE_ALWAYS_INLINE { f(i, j); });
+    });
+  }
+
+  // K values [kbeg, kbeg + K) of A's rows m0.. (of M) and B's rows n0.. (of N).
+  __device__ __forceinline__ static void run(const Operand &A, int m0, int M, const Operand &B, int n0, int N, int kbeg,
+                                             int K, int tid, char *smem, Acc &acc) {
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int nk = (K + 63) / 64;
+    TA ta;
+    TB tb;
+    ta.init(A, m0, M, kbeg, tid, (wave / WAVES_N) * WM, lane, smem);
+    tb.init(B, n0, N, kbeg, tid, (wave % WAVES_N) * WN, lane, smem + TA::BYTES);
+    const uint32_t lds_wave =
+        static_cast<uint32_t>(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) char *)smem)) + wave * 1024;
+    // the next stage to load, in the tile's order of parts
+    const int order = PARTS > 1 ? m0 / BM / 8 % PARTS : 0;
+    const int plen = (nk / PARTS) | 1;
+    auto part_begin = [&](int p) EE_ALWAYS_INLINE { return PARTS > 1 ? (p < PARTS ? min(p * plen, nk) : nk) : p * nk; };
+    int l_part = 0, l_t = part_begin(order), l_end = part_begin(order + 1), left = nk;  // left: stages not yet loaded
+    auto load = [&](int buf) EE_ALWAYS_INLINE {
+      if constexpr (PARTS > 1) {
+        while (l_t == l_end && l_part < PARTS - 1) {  // (a part may be empty)
+          ++l_part;
+          l_t = part_begin(l_part ^ order);
+          l_end = part_begin((l_part ^ order) + 1);
+        }
+      }
+      ta.load(l_t, K - l_t * 64, lds_wave + buf * STAGE_BYTES);
+      tb.load(l_t, K - l_t * 64, lds_wave + buf * STAGE_BYTES + TA::BYTES);
+      ++l_t;
+      --left;
+    };
+    static_for<NS - 1>([&](auto t) EE_ALWAYS_INLINE {
+      if (decltype(t)::value < nk) load(decltype(t)::value);
+    });
+    int cur = 0;  // buffer of the stage to consume
+    int todo = nk;
+    auto consume = [&]() EE_ALWAYS_INLINE {
+      // it has landed when at most the later stages' loads are in flight
+      const int later = min(todo - 1, NS - 2);
+      static_for<NS - 1>([&](auto l) EE_ALWAYS_INLINE {
+        if (later == decltype(l)::value) wait_vm<decltype(l)::value * LOADS>();
+      });
+      if constexpr (!AK) {
+        if (todo == 1 && K % 64 != 0) {  // zero A's k-rows past K, each thread the chunks it loaded itself
+          ta.zero_tail(K - (nk - 1) * 64, tid, smem + cur * STAGE_BYTES);
+          wait_lgkm();
+        }
+      }
+      phase_barrier();
+      if (left > 0) load(cur == 0 ? NS - 1 : cur - 1);  // over the last stage, which every wave has read
+      const int stage = cur * STAGE_BYTES;
+      static_for<2>([&](auto ks) EE_ALWAYS_INLINE {
+        bf16x8_t fa[WM / 16], fb[WN / 16];
+        tb.template read<decltype(ks)::value>(stage, fb);
+        ta.template read<decltype(ks)::value>(stage, fa);
+        each([&](auto i, auto j) EE_ALWAYS_INLINE {
+          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[i], fb[j], acc[i][j], 0, 0, 0);
+        });
+      });
+      wait_lgkm();
+      cur = cur == NS - 1 ? 0 : cur + 1;
+      --todo;
+    };
+    constexpr int LEVELS = PARTS == 1 ? 1 : PARTS == 4 ? 2 : 3;
+    Acc sum[LEVELS];  // sum[l]: the finished first half of a group of 2^(l+1) parts
+    static_for<PARTS>([&](auto p_) EE_ALWAYS_INLINE {
+      constexpr int P = decltype(p_)::value;
+      each([&](auto i, auto j) EE_ALWAYS_INLINE { acc[i][j] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f}; });
+      const int p = P ^ order, len = part_begin(p + 1) - part_begin(p);
+      for (int t = 0; t < len; ++t) consume();
+      if constexpr (PARTS > 1) {
+        constexpr int FULL = P == PARTS - 1 ? LEVELS : __builtin_ctz(~P);  // groups that end with this part
+        each([&](auto i, auto j) EE_ALWAYS_INLINE {
+          static_for<FULL>([&](auto l) EE_ALWAYS_INLINE { acc[i][j] += sum[l][i][j]; });
+          if constexpr (FULL < LEVELS) sum[FULL][i][j] = acc[i][j];
+        });
+      }
+    });
+    phase_barrier();
+  }
+};
+
+}  // namespace ee

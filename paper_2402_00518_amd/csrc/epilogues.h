@@ -168,6 +168,7 @@ template <typename T> using Raw4 = typename Raw4Of<T>::type;
 // zeros, so they must be finite (the seed zeroes them).
 template <typename T>
 struct EpiLogits {
+  static constexpr int kBarriers = 2;
   struct Params {
     T *P;               // [V][ldp]
     int64_t ldp;        // padded token count (multiple of 8)
@@ -355,6 +356,7 @@ struct EpiLogits {
 // block's W loads have been consumed, so no store waits on a load.
 template <typename T>
 struct EpiWeightGrad {
+  static constexpr int kBarriers = 2;
   static constexpr bool kPersistent = true;  // launch_gemm runs it as one block per CU looping over the tiles
   struct Params {
     float *dW;          // [N][ldw]

@@ -4,19 +4,17 @@
 //
 // Each operand is either K-major (element (r, k) at ptr[r*ld + k], K
 // contiguous) or MN-major (element (r, k) at ptr[k*ld + r], rows
-// contiguous).  K-major tiles sit in LDS as rows of K; bf16 MN-major tiles
-// are copied as they are (k-rows) and transposed by the fragment reads
-// themselves (ds_read_b64_tr_b16), so neither side spends ALU work on the
-// layout.  (fp32 MN-major operands are transposed in registers on their way
-// into LDS.)
+// contiguous).  Operand tiles go from memory straight into LDS
+// (global_load_lds_dwordx4), as they are: K-major tiles as rows of K, MN-major
+// tiles as k-rows, which bf16 fragment reads transpose (ds_read_b64_tr_b16), so
+// neither side spends ALU work or registers on the way.
 //
-// bf16 products (gemm_block_b16) run a 256 x 256 tile on 8 wave64 waves of
-// 128 x 64, v_mfma_f32_16x16x32_bf16: operand tiles go from memory straight
-// into LDS (global_load_lds_dwordx4, two stages of 64 values of K) and the
-// two waves of a SIMD take turns, one in its MFMAs while the other reads its
-// fragments.  fp32 products (gemm_block) run a 128 x 128 tile on 4 waves,
-// v_mfma_f32_32x32x2_f32, staged through registers.  Both accumulate in fp32
-// and hand their epilogue 32 x 32 blocks (TileCtx).
+// bf16 products (v_mfma_f32_16x16x32_bf16) run a 256 x 256 tile on 8 wave64
+// waves of 128 x 64, the two waves of a SIMD taking turns, one in its MFMAs
+// while the other reads its fragments; where few such tiles exist, a 128 x 128
+// tile on 4 waves of 64 x 64 with a ring of stages (ring.h).  fp32 products
+// (v_mfma_f32_32x32x2_f32) run the ring on 128 x 128 or 64 x 64.  All
+// accumulate in fp32 and hand their epilogue 32 x 32 blocks (TileCtx).
 //
 // Blocks are ordered for the L2 of each XCD: the hardware hands block b to
 // XCD b % 8, so consecutive logical tiles are given to the same XCD, and
@@ -25,7 +23,6 @@
 #pragma once
 
 #include <algorithm>
-#include <cstdlib>
 
 #include "ee_device.h"
 #include "ring.h"
@@ -42,26 +39,29 @@ constexpr int kNumXcd = 8;
 constexpr int kGroupM = 4;
 constexpr int kLoopBlocks = 256;  // grid of the looping kernels: one block per CU of a 256-CU GPU (a multiple of kNumXcd)
 
-template <int BM_, int BN_, int WM_, int WN_, int MIN_BLOCKS_, int STAGES_ = 2>
+template <int BM_, int BN_, int WM_, int WN_, int MIN_BLOCKS_, int STAGES_ = 2, int KW_ = 1>
 struct TileCfg {
   static constexpr int BM = BM_, BN = BN_, WM = WM_, WN = WN_;
   static constexpr int MIN_BLOCKS = MIN_BLOCKS_;  // workgroups per CU the registers must allow
   static constexpr int WAVES_M = BM / WM, WAVES_N = BN / WN;
   static constexpr int THREADS = WAVES_M * WAVES_N * 64;
+  static constexpr int KW = KW_;                 // waves that share a wave's tile, each a part of K (fp32)
+  static constexpr int BLOCK = THREADS * KW;     // threads of a workgroup
   static constexpr int MB = WM / 32, NB = WN / 32;
   static constexpr int STAGE_BYTES = (BM + BN) * kRowBytes;
   static constexpr int STAGES = STAGES_;  // LDS stages
   static constexpr int SMEM_BYTES = STAGES * STAGE_BYTES;
 };
-// 128 x 128 tile, 64 x 64 per wave: every fp32 GEMM.
-using CfgSmall = TileCfg<128, 128, 64, 64, 2>;
 // 256 x 256 tile, 8 waves of 128 x 64 (two waves per SIMD): every bf16 GEMM.
 // 1.5x the MFMA work per byte read from LDS of the small tile, and a second
 // wave per SIMD to issue while the other waits.
 using CfgBig = TileCfg<256, 256, 128, 64, 1>;
 // 128 x 128 tile, 64 x 64 per wave, a ring of 4 stages: bf16 products with too
 // few 256 x 256 tiles to fill the chip.
-using CfgMid = TileCfg<128, 128, 64, 64, 1, 4>;
+using CfgMid = TileCfg<128, 128, 64, 64, 2, 2>;
+// fp32: 128 x 128 on 4 waves of 64 x 64, or 64 x 64 on 4 waves that share K.
+using CfgF32 = TileCfg<128, 128, 64, 64, 2, 2>;
+using CfgF32Small = TileCfg<64, 64, 64, 64, 2, 4, 4>;
 
 template <typename T> struct Elem;
 template <> struct Elem<bf16_t> {
@@ -73,107 +73,6 @@ template <> struct Elem<float> {
 
 __host__ __device__ constexpr int cdiv(int64_t a, int64_t b) { return static_cast<int>((a + b - 1) / b); }
 
-// Byte offset of 16-byte chunk `ch` (0..7) of K-major LDS tile row `row`.
-// A ds_read_b128 is served 16 lanes at a time from 256 bytes of banks, i.e.
-// two 128-byte tile rows; the 16 lanes of a fragment read read 16
-// consecutive rows at one logical chunk, so within every aligned group of 16
-// rows, rows of equal parity must land on distinct chunks: the XOR key is
-// (row / 2) mod 8.  It repeats every 16 rows, so a lane's fragment rows 32
-// apart share one swizzle and their addresses differ by a constant.
-__device__ __forceinline__ int lds_off(int row, int ch) {
-  return row * kRowBytes + ((ch ^ ((row >> 1) & 7)) << 4);
-}
-
-// ---------------------------------------------------------------- loaders
-// K-major tile: ROWS rows x 8 chunks of 16 bytes.  Each thread's byte
-// offsets inside the tile's row panel are computed once (32-bit: a panel
-// spans at most ROWS x 32768 x 4 bytes); per stage only the uniform panel
-// base moves, so every load is a scalar base plus a per-thread offset.
-template <typename T, int ROWS, int THREADS, int GROUPS>
-struct KMajorLoader {
-  static constexpr int CH = Elem<T>::CH;
-  static constexpr int PER = ROWS * 8 / THREADS;  // 16-byte loads per thread per stage
-  static constexpr int PG = PER / GROUPS;         // loads per group
-  static_assert(PER % GROUPS == 0, "stage loads must split evenly over the substeps");
-  u32x4_t reg[PER];
-  uint32_t off[PER];
-
-  // Rows past the operand's end are clamped to its last row: they only feed
-  // output rows or columns that the epilogues never store.
-  __device__ __forceinline__ void init(int64_t ld, int row0, int rows, int /*K*/, int tid) {
-    static_for<PER>([&](auto i) EE_ALWAYS_INLINE {
-      const int c = tid + i * THREADS;
-      const int r = min(row0 + (c >> 3), rows - 1) - row0;
-      off[i] = static_cast<uint32_t>((static_cast<int64_t>(r) * ld + (c & 7) * CH) * sizeof(T));
-    });
-  }
-  // Group g of the stage starting at K offset k0 (a multiple of the stage
-  // depth; K itself is one too, checked by the launcher): no load is
-  // predicated, since predicated loads would split the code into blocks
-  // across which the compiler can only wait for every outstanding load.
-  template <int G>
-  __device__ __forceinline__ void load(const T *base, int64_t ld, int row0, int k0) {
-    const char *panel = reinterpret_cast<const char *>(base + static_cast<int64_t>(row0) * ld + k0);
-    static_for<PG>([&](auto q) EE_ALWAYS_INLINE {
-      constexpr int i = G * PG + decltype(q)::value;
-      reg[i] = *reinterpret_cast<const u32x4_t *>(panel + off[i]);
-    });
-  }
-  template <int G>
-  __device__ __forceinline__ void store(char *lds, int tid) const {
-    static_for<PG>([&](auto q) EE_ALWAYS_INLINE {
-      constexpr int i = G * PG + decltype(q)::value;
-      const int c = tid + i * THREADS;
-      *reinterpret_cast<u32x4_t *>(lds + lds_off(c >> 3, c & 7)) = reg[i];
-    });
-  }
-};
-
-// K-major tile whose rows come from two matrices of equal shape, F rows
-// each (F a multiple of 32), interleaved in blocks of 32: tile-space row r
-// is row (r / 64) * 32 + r % 32 of the first matrix when (r / 32) is even,
-// of the second when it is odd.  A wave whose columns are 64 tile rows wide
-// then holds both matrices' products for the same 32 rows in its two
-// 32-column blocks (the gate and up projections of one set of features).
-// Tile rows past 2F are clamped to the last row of the second matrix.
-template <typename T, int ROWS, int THREADS, int GROUPS>
-struct KMajorPairLoader {
-  static constexpr int CH = Elem<T>::CH;
-  static constexpr int PER = ROWS * 8 / THREADS;
-  static constexpr int PG = PER / GROUPS;
-  static_assert(PER % GROUPS == 0, "stage loads must split evenly over the substeps");
-  static_assert(ROWS % 64 == 0, "the tile must hold whole 64-row pairs");
-  u32x4_t reg[PER];
-  int64_t off[PER];  // bytes from the first matrix's row row0 / 2
-
-  // row0: the tile's first tile-space row (a multiple of 64); rows: 2F.
-  __device__ __forceinline__ void init(int64_t ld, int row0, int rows, int64_t pair, int tid) {
-    static_for<PER>([&](auto i) EE_ALWAYS_INLINE {
-      const int c = tid + i * THREADS;
-      const int r = min(row0 + (c >> 3), rows - 1);   // tile-space row
-      const int f = (r >> 6) * 32 + (r & 31) - row0 / 2;  // row of its matrix, from row0 / 2
-      off[i] = (static_cast<int64_t>(f) * ld + (c & 7) * CH) * static_cast<int64_t>(sizeof(T)) +
-               (((r >> 5) & 1) ? pair : 0);
-    });
-  }
-  template <int G>
-  __device__ __forceinline__ void load(const T *base, int64_t ld, int row0, int k0) {
-    const char *panel = reinterpret_cast<const char *>(base + static_cast<int64_t>(row0 / 2) * ld + k0);
-    static_for<PG>([&](auto q) EE_ALWAYS_INLINE {
-      constexpr int i = G * PG + decltype(q)::value;
-      reg[i] = *reinterpret_cast<const u32x4_t *>(panel + off[i]);
-    });
-  }
-  template <int G>
-  __device__ __forceinline__ void store(char *lds, int tid) const {
-    static_for<PG>([&](auto q) EE_ALWAYS_INLINE {
-      constexpr int i = G * PG + decltype(q)::value;
-      const int c = tid + i * THREADS;
-      *reinterpret_cast<u32x4_t *>(lds + lds_off(c >> 3, c & 7)) = reg[i];
-    });
-  }
-};
-
 // Epilogues that take the B operand as an interleaved pair declare
 // kPairB = true.
 template <class E, class = void> struct EpiPairB : std::false_type {};
@@ -183,101 +82,11 @@ template <class E, class = void> struct EpiPersistent : std::false_type {};
 template <class E>
 struct EpiPersistent<E, std::void_t<decltype(E::kPersistent)>> : std::bool_constant<E::kPersistent> {};
 
-// MN-major tile: BK k-rows x ROWS contiguous operand rows, written
-// transposed (k contiguous) into LDS.
-template <typename T, int ROWS, int THREADS> struct MNMajorLoader;
-
-// Adapter giving the fp32 MN-major loader the grouped interface: the whole
-// stage is loaded and stored by group 0.
-template <typename T, int ROWS, int THREADS, int GROUPS>
-struct MNMajorLoaderGrouped : MNMajorLoader<T, ROWS, THREADS> {
-  int rows_, K_, tid_;
-  __device__ __forceinline__ void init(int64_t, int, int rows, int K, int tid) {
-    rows_ = rows;
-    K_ = K;
-    tid_ = tid;
-  }
-  template <int G>
-  __device__ __forceinline__ void load(const T *base, int64_t ld, int row0, int k0) {
-    if constexpr (G == 0) MNMajorLoader<T, ROWS, THREADS>::load(base, ld, row0, rows_, k0, K_, tid_);
-  }
-  template <int G>
-  __device__ __forceinline__ void store(char *lds, int tid) const {
-    if constexpr (G == 0) MNMajorLoader<T, ROWS, THREADS>::store(lds, tid);
-  }
-};
-
-template <int ROWS, int THREADS> struct MNMajorLoader<float, ROWS, THREADS> {
-  static constexpr int GROUPS = ROWS / 4;
-  static constexpr int PER = (32 / 4) * GROUPS / THREADS;
-  u32x4_t reg[PER][4];  // reg[p][r] = 4 values of k-row r
-
-  __device__ __forceinline__ void load(const float *base, int64_t ld, int row0, int rows,
-                                       int k0, int K, int tid) {
-#pragma unroll
-    for (int p = 0; p < PER; ++p) {
-      const int b = tid + p * THREADS;
-      const int kb = b / GROUPS, mb = b % GROUPS;
-      const int m = min(row0 + mb * 4, rows - 4);  // rows is a multiple of 4
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int k = k0 + kb * 4 + r;
-        const u32x4_t v = *reinterpret_cast<const u32x4_t *>(base + static_cast<int64_t>(min(k, K - 1)) * ld + m);
-        reg[p][r] = k < K ? v : u32x4_t{0, 0, 0, 0};
-      }
-    }
-  }
-  __device__ __forceinline__ void store(char *lds, int tid) const {
-#pragma unroll
-    for (int p = 0; p < PER; ++p) {
-      const int b = tid + p * THREADS;
-      const int kb = b / GROUPS, mb = b % GROUPS;
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const u32x4_t v = {reg[p][0][j], reg[p][1][j], reg[p][2][j], reg[p][3][j]};
-        *reinterpret_cast<u32x4_t *>(lds + lds_off(mb * 4 + j, kb)) = v;
-      }
-    }
-  }
-};
-
-template <bool KMajor, int ROWS, int THREADS, int GROUPS>
-using F32Loader = std::conditional_t<KMajor, KMajorLoader<float, ROWS, THREADS, GROUPS>,
-                                     MNMajorLoaderGrouped<float, ROWS, THREADS, GROUPS>>;
-
-// ------------------------------------------------------------ MFMA step
-// fp32 fragments of one K substep (16 values of K) for the wave's MB x NB
-// blocks of 32 x 32, read from one LDS stage, and the MFMAs that consume them.
-template <class Cfg> struct FragsF32 {
-  static constexpr int MB = Cfg::MB, NB = Cfg::NB;
-  static constexpr int SUBSTEPS = 2;  // 2 x 16 = 32 values of K per stage
-  static constexpr int MMAS = 8 * MB * NB;  // MFMAs per substep
-  f32x4_t a[MB][2], b[NB][2];
-
-  __device__ __forceinline__ void load(const char *a_lds, const char *b_lds, int a_row0, int b_row0, int lane, int s) {
-    const int r = lane & 31, half = lane >> 5;
-    static_for<2>([&](auto c) EE_ALWAYS_INLINE {
-      const int ch = s * 4 + half * 2 + c;
-      static_for<MB>([&](auto i) EE_ALWAYS_INLINE {
-        a[i][c] = *reinterpret_cast<const f32x4_t *>(a_lds + lds_off(a_row0 + i * 32 + r, ch));
-      });
-      static_for<NB>([&](auto j) EE_ALWAYS_INLINE {
-        b[j][c] = *reinterpret_cast<const f32x4_t *>(b_lds + lds_off(b_row0 + j * 32 + r, ch));
-      });
-    });
-  }
-  __device__ __forceinline__ void mma(f32x16_t (&acc)[MB][NB]) const {
-    static_for<8>([&](auto e) EE_ALWAYS_INLINE {
-      static_for<MB>([&](auto i) EE_ALWAYS_INLINE {
-        static_for<NB>([&](auto j) EE_ALWAYS_INLINE {
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i][e / 4][decltype(e)::value % 4],
-                                                            b[j][e / 4][decltype(e)::value % 4], acc[i][j],
-                                                            0, 0, 0);
-        });
-      });
-    });
-  }
-};
+// Barriers an epilogue passes (kBarriers; waves without a tile of their own
+// pass them too).
+template <class E, class = void> struct EpiBarriers : std::integral_constant<int, 0> {};
+template <class E>
+struct EpiBarriers<E, std::void_t<decltype(E::kBarriers)>> : std::integral_constant<int, E::kBarriers> {};
 
 // Position of accumulator element (i, j, v) of a lane:
 //   row = m0 + wave_m*WM + i*32 + (v/4)*8 + (lane/32)*4 + v%4
@@ -332,116 +141,28 @@ struct GemmBlock;
 // fp32.
 template <bool AK, bool BKM, class Epi, class Cfg, bool LOOP>
 struct GemmBlock<float, AK, BKM, Epi, Cfg, LOOP> {
-static __device__ __forceinline__ void run(const Operand &A, const Operand &B, const GemmShape &s,
-                                           const typename Epi::Params &ep, int b, int nblk, int kz, char *smem) {
-  constexpr int BK = 8 * Elem<float>::CH;
-  constexpr int MB = Cfg::MB, NB = Cfg::NB;
-  int tid_v = threadIdx.x;
-  if constexpr (LOOP) asm volatile("" : "+v"(tid_v));
-  const int tid = tid_v, lane = tid & 63, wave = tid >> 6;
-  const int wave_m = wave / Cfg::WAVES_N, wave_n = wave % Cfg::WAVES_N;
-  const int tiles_m = cdiv(s.M, Cfg::BM), tiles_n = cdiv(s.N, Cfg::BN);
-  int tile_m, tile_n;
-  tile_of_block(b, nblk, tiles_m, tiles_n, tile_m, tile_n);
-  const int m0 = tile_m * Cfg::BM, n0 = tile_n * Cfg::BN;
-  const float *a_ptr = static_cast<const float *>(A.ptr);
-  const float *b_ptr = static_cast<const float *>(B.ptr);
-
-  using F = FragsF32<Cfg>;
-  constexpr int SUB = F::SUBSTEPS;
-  constexpr bool kPair = EpiPairB<Epi>::value;
-  static_assert(!kPair || BKM, "an interleaved pair is read K-major");
-  F32Loader<AK, Cfg::BM, Cfg::THREADS, SUB> la;
-  std::conditional_t<kPair, KMajorPairLoader<float, Cfg::BN, Cfg::THREADS, SUB>,
-                     F32Loader<BKM, Cfg::BN, Cfg::THREADS, SUB>>
-      lb;
-  la.init(A.ld, m0, s.M, s.K, tid);
-  if constexpr (kPair)
-    lb.init(B.ld, n0, s.N, B.pair, tid);
-  else
-    lb.init(B.ld, n0, s.N, s.K, tid);
-  f32x16_t acc[MB][NB];
-  static_for<MB>([&](auto i) EE_ALWAYS_INLINE {
-    static_for<NB>([&](auto j) EE_ALWAYS_INLINE {
-      static_for<16>([&](auto v) EE_ALWAYS_INLINE { acc[i][j][decltype(v)::value] = 0.0f; });
-    });
-  });
-
-  // Software pipeline over K stages (BK values of K each).  Registers hold
-  // stage kt + 1 while stage kt is consumed from LDS.  Each of the stage's
-  // substeps (16 values of K) interleaves, MFMA by MFMA:
-  //   * the fragment reads of the next substep,
-  //   * its share of the LDS writes of stage kt + 1 (the other buffer),
-  //   * its share of the global loads of stage kt + 2 into the registers
-  //     those writes just drained.
-  // A wave issues in order, so bursts of memory instructions would hold up
-  // its MFMAs; spread out, they issue while the matrix core is busy.  The
-  // writes of stage kt + 1 are finished by the second-to-last substep; the
-  // barrier follows it, and the last substep then reads the first fragments
-  // of stage kt + 1 while its own MFMAs run, so no stage starts by waiting
-  // for LDS.  The code of a stage has no branches (loads past the last
-  // stage re-read it), so the scheduler sees each stage as one region.
-  constexpr int B_OFF = Cfg::BM * kRowBytes;
-  const int kbeg = s.kchunk > 0 ? kz * s.kchunk : 0;
-  const int kend = s.kchunk > 0 ? min(s.K, kbeg + s.kchunk) : s.K;
-  const int nk = cdiv(kend - kbeg, BK);
-  const int a_row0 = wave_m * Cfg::WM, b_row0 = wave_n * Cfg::WN;
-  static_for<SUB>([&](auto g) EE_ALWAYS_INLINE {
-    la.template load<decltype(g)::value>(a_ptr, A.ld, m0, kbeg);
-    lb.template load<decltype(g)::value>(b_ptr, B.ld, n0, kbeg);
-  });
-  static_for<SUB>([&](auto g) EE_ALWAYS_INLINE {
-    la.template store<decltype(g)::value>(smem, tid);
-    lb.template store<decltype(g)::value>(smem + B_OFF, tid);
-  });
-  const int k1 = kbeg + min(1, nk - 1) * BK;
-  static_for<SUB>([&](auto g) EE_ALWAYS_INLINE {
-    la.template load<decltype(g)::value>(a_ptr, A.ld, m0, k1);
-    lb.template load<decltype(g)::value>(b_ptr, B.ld, n0, k1);
-  });
-  __syncthreads();
-  F f0, f1;
-  f0.load(smem, smem + B_OFF, a_row0, b_row0, lane, 0);
-  for (int kt = 0; kt < nk; ++kt) {
-    const char *cur = smem + (kt & 1) * Cfg::STAGE_BYTES;
-    char *next = smem + ((kt + 1) & 1) * Cfg::STAGE_BYTES;
-    const int k2 = kbeg + min(kt + 2, nk - 1) * BK;
-    static_for<SUB>([&](auto st) EE_ALWAYS_INLINE {
-      constexpr int sub = decltype(st)::value;
-      F &now = (sub % 2 == 0) ? f0 : f1;
-      F &later = (sub % 2 == 0) ? f1 : f0;
-      if constexpr (sub + 1 < SUB)
-        later.load(cur, cur + B_OFF, a_row0, b_row0, lane, sub + 1);
-      else
-        later.load(next, next + B_OFF, a_row0, b_row0, lane, 0);  // next stage, published by the barrier
-      if constexpr (sub < SUB - 2) {
-        la.template store<sub>(next, tid);
-        lb.template store<sub>(next + B_OFF, tid);
-        la.template load<sub>(a_ptr, A.ld, m0, k2);
-        lb.template load<sub>(b_ptr, B.ld, n0, k2);
-      } else if constexpr (sub == SUB - 2) {
-        static_for<2>([&](auto gg) EE_ALWAYS_INLINE {
-          constexpr int g = SUB - 2 + decltype(gg)::value;
-          la.template store<g>(next, tid);
-          lb.template store<g>(next + B_OFF, tid);
-          la.template load<g>(a_ptr, A.ld, m0, k2);
-          lb.template load<g>(b_ptr, B.ld, n0, k2);
-        });
-      }
-      now.mma(acc);
-      static_for<F::MMAS>([&](auto) EE_ALWAYS_INLINE {
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // MFMA
-        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);  // DS read
-        __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);  // DS write
-        __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);  // VMEM read
-      });
-      if constexpr (sub == SUB - 2) __syncthreads();
-    });
+  static __device__ __forceinline__ void run(const Operand &A, const Operand &B, const GemmShape &s,
+                                             const typename Epi::Params &ep, int b, int nblk, int kz, char *smem) {
+    using R = RingF32<Cfg::BM, Cfg::BN, Cfg::KW, Cfg::STAGES, AK, BKM, EpiPairB<Epi>::value>;
+    static_assert(R::THREADS == Cfg::BLOCK && (!LOOP || Cfg::KW == 1), "waves of 64 x 64");
+    int tid_v = threadIdx.x;
+    if constexpr (LOOP) asm volatile("" : "+v"(tid_v));
+    const int tid = tid_v, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    int tile_m, tile_n;
+    tile_of_block(b, nblk, cdiv(s.M, Cfg::BM), cdiv(s.N, Cfg::BN), tile_m, tile_n);
+    const int m0 = tile_m * Cfg::BM, n0 = tile_n * Cfg::BN;
+    const int kbeg = s.kchunk > 0 ? kz * s.kchunk : 0;
+    const int K = (s.kchunk > 0 ? min(s.K, kbeg + s.kchunk) : s.K) - kbeg;
+    f32x16_t acc[2][2];
+    R::run(A, m0, s.M, B, n0, s.N, kbeg, K, tid, smem, acc);
+    if (Cfg::KW > 1 && wave > 0) {  // the first wave holds the tile
+      static_for<EpiBarriers<Epi>::value>([&](auto) EE_ALWAYS_INLINE { __syncthreads(); });
+      return;
+    }
+    const int w = Cfg::KW > 1 ? 0 : wave;
+    TileCtx<Cfg> ctx{s.M, s.N, m0, n0, tile_m, tile_n, w / Cfg::WAVES_N, w % Cfg::WAVES_N, lane, smem, kz};
+    Epi::template apply<Cfg>(ep, acc, ctx);
   }
-
-  TileCtx<Cfg> t{s.M, s.N, m0, n0, tile_m, tile_n, wave_m, wave_n, lane, smem, kz};
-  Epi::template apply<Cfg>(ep, acc, t);
-}
 };
 
 // ------------------------------------------------------------ bf16 main loop
@@ -736,9 +457,9 @@ __device__ __forceinline__ void gemm_block(const Operand &A, const Operand &B, c
 }
 
 template <typename T, bool AK, bool BKM, class Epi, class Cfg>
-__global__ __launch_bounds__(Cfg::THREADS, Cfg::MIN_BLOCKS) void gemm_kernel(Operand A, Operand B, GemmShape s,
+__global__ __launch_bounds__(Cfg::BLOCK, Cfg::MIN_BLOCKS) void gemm_kernel(Operand A, Operand B, GemmShape s,
                                                                 typename Epi::Params ep) {
-  __shared__ __attribute__((aligned(16))) char smem[Cfg::SMEM_BYTES];
+  __shared__ __attribute__((aligned(128))) char smem[Cfg::SMEM_BYTES];
   gemm_block<T, AK, BKM, Epi, Cfg>(A, B, s, ep, blockIdx.x, gridDim.x, blockIdx.z, smem);
 }
 
@@ -749,9 +470,9 @@ __global__ __launch_bounds__(Cfg::THREADS, Cfg::MIN_BLOCKS) void gemm_kernel(Ope
 // XCD-aware order; when the flag is clear the launch costs one round of
 // blocks that read it and return.
 template <typename T, bool AK, bool BKM, class Epi, class Cfg>
-__global__ __launch_bounds__(Cfg::THREADS, Cfg::MIN_BLOCKS) void gemm_gated_kernel(Operand A, Operand B, GemmShape s,
+__global__ __launch_bounds__(Cfg::BLOCK, Cfg::MIN_BLOCKS) void gemm_gated_kernel(Operand A, Operand B, GemmShape s,
                                                                       typename Epi::Params ep, const int *run_if) {
-  __shared__ __attribute__((aligned(16))) char smem[Cfg::SMEM_BYTES];
+  __shared__ __attribute__((aligned(128))) char smem[Cfg::SMEM_BYTES];
   if (*run_if == 0) return;  // the same word for every thread
   const int tiles = cdiv(s.M, Cfg::BM) * cdiv(s.N, Cfg::BN);
   for (int t = blockIdx.x; t < tiles; t += gridDim.x) {
@@ -767,10 +488,10 @@ __global__ __launch_bounds__(Cfg::THREADS, Cfg::MIN_BLOCKS) void gemm_gated_kern
 // between one weight-gradient tile's end and the next one's start on the
 // freed CU).
 template <typename T, bool AK, bool BKM, class Epi, class Cfg>
-__global__ __launch_bounds__(Cfg::THREADS, Cfg::MIN_BLOCKS) void gemm_persistent_kernel(Operand A, Operand B,
+__global__ __launch_bounds__(Cfg::BLOCK, Cfg::MIN_BLOCKS) void gemm_persistent_kernel(Operand A, Operand B,
                                                                            GemmShape s,
                                                                            typename Epi::Params ep) {
-  __shared__ __attribute__((aligned(16))) char smem[Cfg::SMEM_BYTES];
+  __shared__ __attribute__((aligned(128))) char smem[Cfg::SMEM_BYTES];
   const int tiles = cdiv(s.M, Cfg::BM) * cdiv(s.N, Cfg::BN);
   for (int t = blockIdx.x; t < tiles; t += gridDim.x) {
     gemm_block<T, AK, BKM, Epi, Cfg, true>(A, B, s, ep, t, tiles, 0, smem);
@@ -786,10 +507,10 @@ __global__ __launch_bounds__(Cfg::THREADS, Cfg::MIN_BLOCKS) void gemm_persistent
 // leaves CUs idle.  Problem 2 may be split along K (s2.kchunk > 0): its
 // blocks then run slice by slice, each slice over all of its tiles.
 template <typename T, bool AK1, bool BKM1, class Epi1, bool AK2, bool BKM2, class Epi2, class Cfg>
-__global__ __launch_bounds__(Cfg::THREADS, Cfg::MIN_BLOCKS) void gemm_pair_kernel(
+__global__ __launch_bounds__(Cfg::BLOCK, Cfg::MIN_BLOCKS) void gemm_pair_kernel(
     Operand A1, Operand B1, GemmShape s1, typename Epi1::Params ep1, Operand A2, Operand B2, GemmShape s2,
     typename Epi2::Params ep2, int blocks1, int base2) {
-  __shared__ __attribute__((aligned(16))) char smem[Cfg::SMEM_BYTES];
+  __shared__ __attribute__((aligned(128))) char smem[Cfg::SMEM_BYTES];
   const int b = blockIdx.x;
   if (b < blocks1)
     gemm_block<T, AK1, BKM1, Epi1, Cfg>(A1, B1, s1, ep1, b, blocks1, 0, smem);
@@ -803,10 +524,10 @@ __global__ __launch_bounds__(Cfg::THREADS, Cfg::MIN_BLOCKS) void gemm_pair_kerne
 // block t on block t mod gridDim.x, a multiple of 8), for two
 // weight-gradient products.
 template <typename T, bool AK1, bool BKM1, class Epi1, bool AK2, bool BKM2, class Epi2, class Cfg>
-__global__ __launch_bounds__(Cfg::THREADS, Cfg::MIN_BLOCKS) void gemm_pair_persistent_kernel(
+__global__ __launch_bounds__(Cfg::BLOCK, Cfg::MIN_BLOCKS) void gemm_pair_persistent_kernel(
     Operand A1, Operand B1, GemmShape s1, typename Epi1::Params ep1, Operand A2, Operand B2, GemmShape s2,
     typename Epi2::Params ep2, int blocks1, int base2, int total) {
-  __shared__ __attribute__((aligned(16))) char smem[Cfg::SMEM_BYTES];
+  __shared__ __attribute__((aligned(128))) char smem[Cfg::SMEM_BYTES];
   const int tiles2 = cdiv(s2.M, Cfg::BM) * cdiv(s2.N, Cfg::BN);
   for (int t = blockIdx.x; t < total; t += gridDim.x) {
     if (t < blocks1) {
@@ -842,13 +563,13 @@ hipError_t launch_gemm(Operand A, Operand B, GemmShape s, const typename Epi::Pa
   }
   if constexpr (EpiPersistent<Epi>::value && std::is_same<T, bf16_t>::value) {
     if (splits == 1 && blocks > 2 * kLoopBlocks) {
-      hipLaunchKernelGGL((gemm_persistent_kernel<T, AK, BKM, Epi, Cfg>), dim3(kLoopBlocks), dim3(Cfg::THREADS), 0,
+      hipLaunchKernelGGL((gemm_persistent_kernel<T, AK, BKM, Epi, Cfg>), dim3(kLoopBlocks), dim3(Cfg::BLOCK), 0,
                          stream, A, B, s, ep);
       return hipGetLastError();
     }
   }
   hipLaunchKernelGGL((gemm_kernel<T, AK, BKM, Epi, Cfg>), dim3(static_cast<unsigned>(blocks), 1, splits),
-                     dim3(Cfg::THREADS), 0, stream, A, B, s, ep);
+                     dim3(Cfg::BLOCK), 0, stream, A, B, s, ep);
   return hipGetLastError();
 }
 
@@ -862,7 +583,7 @@ hipError_t launch_gemm_gated(Operand A, Operand B, GemmShape s, const typename E
   if (s.kchunk != 0 || run_if == nullptr || !gemm_shape_ok<T, AK, BKM>(A, B, s)) return hipErrorInvalidValue;
   const int64_t blocks = std::min<int64_t>(kGatedBlocks, (tiles + kNumXcd - 1) / kNumXcd * kNumXcd);
   hipLaunchKernelGGL((gemm_gated_kernel<T, AK, BKM, Epi, Cfg>), dim3(static_cast<unsigned>(blocks)),
-                     dim3(Cfg::THREADS), 0, stream, A, B, s, ep, run_if);
+                     dim3(Cfg::BLOCK), 0, stream, A, B, s, ep, run_if);
   return hipGetLastError();
 }
 
@@ -886,44 +607,60 @@ hipError_t launch_gemm_pair(Operand A1, Operand B1, GemmShape s1, const typename
   if constexpr (EpiPersistent<Epi1>::value && EpiPersistent<Epi2>::value && std::is_same<T, bf16_t>::value) {
     if (base2 + b2 * splits2 > 2 * kLoopBlocks) {
       hipLaunchKernelGGL((gemm_pair_persistent_kernel<T, AK1, BKM1, Epi1, AK2, BKM2, Epi2, Cfg>), dim3(kLoopBlocks),
-                         dim3(Cfg::THREADS), 0, stream, A1, B1, s1, ep1, A2, B2, s2, ep2, static_cast<int>(b1),
+                         dim3(Cfg::BLOCK), 0, stream, A1, B1, s1, ep1, A2, B2, s2, ep2, static_cast<int>(b1),
                          static_cast<int>(base2), static_cast<int>(base2 + b2 * splits2));
       return hipGetLastError();
     }
   }
   hipLaunchKernelGGL((gemm_pair_kernel<T, AK1, BKM1, Epi1, AK2, BKM2, Epi2, Cfg>),
-                     dim3(static_cast<unsigned>(base2 + b2 * splits2)), dim3(Cfg::THREADS), 0, stream, A1, B1, s1, ep1, A2,
+                     dim3(static_cast<unsigned>(base2 + b2 * splits2)), dim3(Cfg::BLOCK), 0, stream, A1, B1, s1, ep1, A2,
                      B2, s2, ep2, static_cast<int>(b1), static_cast<int>(base2));
   return hipGetLastError();
 }
 
-// bf16 GEMMs take the 256 x 256 tile, or the 128 x 128 tile where that shortens
-// the launch (use_mid_tile); fp32 GEMMs the 128 x 128 tile.
-inline bool use_mid_tile(int64_t big_tiles, int64_t mid_tiles) {
-  static const char *e = getenv("EE_MID");
-  return e ? atoi(e) * big_tiles <= 100 * kLoopBlocks : false;
+// Tile choice.
+// bf16: the 128 x 128 tile where the 256 x 256 tiles fill at most half of the
+// CUs (us, 256 against 128: 80 tiles of K 1024 29 against 20, 64 of K 2048 42
+// against 28, 128 of K 2048 51 against 46, 160 of K 4096 79 against 98).
+inline bool use_mid_tile(int64_t big_tiles) { return big_tiles <= kLoopBlocks / 2; }
+// fp32: rounds of tiles on 256 CUs, the 64 x 64 tile costing 0.3 of a 128 x 128
+// one (us, 128 against 64: 16 tiles of K 512 35 against 13, 128 of K 1000 71
+// against 42, 352 of K 2048 239 against 205, 256 of K 512 43 against 49, 1008
+// of K 512 144 against 179).
+inline bool use_f32_small(int64_t tiles, int64_t small_tiles) {
+  const int64_t r = cdiv(tiles, kLoopBlocks), rs = cdiv(small_tiles, kLoopBlocks);
+  return 3 * rs < 10 * r;
 }
-inline bool use_mid_tile(const GemmShape &s) {
-  return use_mid_tile(static_cast<int64_t>(cdiv(s.M, 256)) * cdiv(s.N, 256), static_cast<int64_t>(cdiv(s.M, 128)) * cdiv(s.N, 128));
+template <class Cfg> int64_t tiles_of(const GemmShape &s) {
+  return static_cast<int64_t>(cdiv(s.M, Cfg::BM)) * cdiv(s.N, Cfg::BN) * (s.kchunk > 0 ? cdiv(s.K, s.kchunk) : 1);
 }
+
+// f(configuration) for the tiles that these products take together.
+template <typename T, class F, class... S>
+hipError_t with_tile(F &&f, const S &...shapes) {
+  if constexpr (std::is_same<T, bf16_t>::value) {
+    if (use_mid_tile((tiles_of<CfgBig>(shapes) + ...))) return f(CfgMid{});
+    return f(CfgBig{});
+  } else {
+    if (use_f32_small((tiles_of<CfgF32>(shapes) + ...), (tiles_of<CfgF32Small>(shapes) + ...))) return f(CfgF32Small{});
+    return f(CfgF32{});
+  }
+}
+
 template <typename T, bool AK, bool BKM, class Epi>
 hipError_t run_gemm(Operand A, Operand B, GemmShape s, const typename Epi::Params &ep, hipStream_t stream) {
-  if constexpr (std::is_same<T, bf16_t>::value) {
-    if (use_mid_tile(s)) return launch_gemm<T, AK, BKM, Epi, CfgMid>(A, B, s, ep, stream);
-    return launch_gemm<T, AK, BKM, Epi, CfgBig>(A, B, s, ep, stream);
-  }
-  else {
-    return launch_gemm<T, AK, BKM, Epi, CfgSmall>(A, B, s, ep, stream);
-  }
+  return with_tile<T>([&](auto c) { return launch_gemm<T, AK, BKM, Epi, decltype(c)>(A, B, s, ep, stream); }, s);
 }
 
 template <typename T, bool AK1, bool BKM1, class Epi1, bool AK2, bool BKM2, class Epi2>
 hipError_t run_gemm_pair(Operand A1, Operand B1, GemmShape s1, const typename Epi1::Params &ep1, Operand A2,
                          Operand B2, GemmShape s2, const typename Epi2::Params &ep2, hipStream_t stream) {
-  if constexpr (std::is_same<T, bf16_t>::value)
-    return launch_gemm_pair<T, AK1, BKM1, Epi1, AK2, BKM2, Epi2, CfgBig>(A1, B1, s1, ep1, A2, B2, s2, ep2, stream);
-  else
-    return launch_gemm_pair<T, AK1, BKM1, Epi1, AK2, BKM2, Epi2, CfgSmall>(A1, B1, s1, ep1, A2, B2, s2, ep2, stream);
+  return with_tile<T>(
+      [&](auto c) {
+        return launch_gemm_pair<T, AK1, BKM1, Epi1, AK2, BKM2, Epi2, decltype(c)>(A1, B1, s1, ep1, A2, B2, s2, ep2,
+                                                                                  stream);
+      },
+      s1, s2);
 }
 
 }  // namespace ee

@@ -4,7 +4,8 @@
 
 namespace ee {
 
-int gemm_part_cols(bool f32) { return f32 ? CfgSmall::WN : CfgBig::WN; }
+static_assert(CfgBig::WN == 64 && CfgMid::WN == 64 && CfgF32::WN == 64 && CfgF32Small::WN == 64, "one slice width");
+int gemm_part_cols(bool) { return CfgBig::WN; }
 
 hipError_t gemm_logits(bool f32, const void *w_out, const void *z, int vocab, int n, int h, void *P, int ldn,
                        float *part_m, float *part_l, float *tgt, const int32_t *targets, hipStream_t stream,
@@ -17,7 +18,7 @@ hipError_t gemm_logits(bool f32, const void *w_out, const void *z, int vocab, in
       if constexpr (std::is_same<T, bf16_t>::value)
         return launch_gemm_gated<T, true, true, EpiLogits<T>, CfgBig>(A, B, sh, ep, run_if, stream);
       else
-        return launch_gemm_gated<T, true, true, EpiLogits<T>, CfgSmall>(A, B, sh, ep, run_if, stream);
+        return launch_gemm_gated<T, true, true, EpiLogits<T>, CfgF32>(A, B, sh, ep, run_if, stream);
     }
     return run_gemm<T, true, true, EpiLogits<T>>(A, B, sh, ep, stream);
   });

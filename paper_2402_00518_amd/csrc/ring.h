@@ -63,37 +63,45 @@ __device__ __forceinline__ void to_blocks32(const f32x4_t (&acc)[2 * MB][2 * NB]
   });
 }
 
-// One operand of a ring stage: ROWS rows by 64 values of K, loaded by THREADS
-// threads, 16 bytes each a load.
+// One operand of a ring stage: ROWS rows by 128 bytes of K (64 bf16 or 32 fp32
+// values), loaded by THREADS threads, 16 bytes each a load.
 // K-major: LDS rows of 128 bytes, 16-byte chunk c of row r at c ^ ((r / 2) mod
 // 8); PAIR: rows of two matrices of F rows each in alternating blocks of 32,
 // tile row r being row (r / 64) * 32 + r % 32 of the first matrix when (r / 32)
 // is even, else of the second (row0 and rows count the interleaved rows).
-// MN-major (128 rows): 64 k-rows of 256 bytes, chunk c of k-row k at c ^ (2 (k
-// mod 4) + 8 (k / 8 mod 2)), read with ds_read_b64_tr_b16: it gives lane 4 a + b
-// of each 16-lane group element b of the 8-byte pieces that lanes a, a + 4,
-// a + 8, a + 12 of the group address.
-template <bool KM, int ROWS, int THREADS, bool PERM, bool PAIR>
+// MN-major: the stage's k-rows as they are in memory.  bf16 (128 rows: k-rows of
+// 256 bytes): chunk c of k-row k at c ^ (2 (k mod 4) + 8 (k / 8 mod 2)), read with
+// ds_read_b64_tr_b16, which gives lane 4 a + b of each 16-lane group element b
+// of the 8-byte pieces that lanes a, a + 4, a + 8, a + 12 of the group address.
+// fp32: an MFMA takes one value a lane, so 32 lanes read 32 rows of a k-row.
+template <typename T, bool KM, int ROWS, int THREADS, bool PERM, bool PAIR>
 struct RingOperand {
+  static constexpr bool kB16 = sizeof(T) == 2;
+  static constexpr int KS = 128 / sizeof(T);  // values of K per stage
   static constexpr int LOADS = ROWS * 8 / THREADS;
   static constexpr int BYTES = ROWS * 128;
+  static constexpr int KROW = ROWS * sizeof(T);   // MN-major: bytes of a k-row in LDS
+  static constexpr int KCH = KROW / 16;           // and its chunks
+  static constexpr int KSTEP = THREADS / KCH;     // k-rows between a thread's chunks
   static_assert(LOADS * THREADS == ROWS * 8, "every thread loads the same number of chunks");
-  static_assert(KM || (ROWS == 128 && !PAIR), "MN-major k-rows are 256 bytes");
+  static_assert(KM || (!PAIR && (!kB16 || ROWS == 128)), "bf16 MN-major k-rows are 256 bytes");
   static_assert(!PAIR || THREADS / 8 <= 32, "a load's rows come from one matrix");
   uint32_t off[LOADS];
-  uint32_t ld2, kr;  // MN-major: bytes per k-row; k-row of the thread's first chunk
-  const char *rd[KM ? 2 : ROWS / 16];
+  uint32_t ldb, kr;  // MN-major: bytes between k-rows; k-row of the thread's first chunk
+  const char *rd[kB16 ? (KM ? 2 : ROWS / 16) : 4];
   const char *base;
   int64_t pair, step;
 
-  __device__ __forceinline__ static int swz(int k) { return 2 * (k & 3) + 8 * ((k >> 3) & 1); }
+  __device__ __forceinline__ static int swz(int k) { return kB16 ? 2 * (k & 3) + 8 * ((k >> 3) & 1) : 0; }
 
   // row0: first (interleaved) row of the tile, rows: rows of the operand;
-  // wrow: the wave's first row in the tile; lds: the operand's LDS in stage 0.
+  // wrow: the wave's first row in the tile; lds: the operand's LDS in stage 0;
+  // kw (fp32): the 8 values of K of each stage from 8 kw on are the wave's, or
+  // -1: all 32.
   __device__ __forceinline__ void init(const Operand &O, int row0, int rows, int kbeg, int tid, int wrow, int lane,
-                                       const char *lds) {
-    const bf16_t *p = static_cast<const bf16_t *>(O.ptr);
-    ld2 = static_cast<uint32_t>(O.ld * 2);
+                                       const char *lds, int kw = -1) {
+    const T *p = static_cast<const T *>(O.ptr);
+    ldb = static_cast<uint32_t>(O.ld * sizeof(T));
     pair = O.pair;
     if constexpr (KM) {
       const int r0 = PAIR ? row0 / 2 : row0, last = (PAIR ? rows / 2 : rows) - 1;
@@ -102,26 +110,38 @@ struct RingOperand {
       static_for<LOADS>([&](auto e) EE_ALWAYS_INLINE {
         const int c = decltype(e)::value * THREADS + tid, lr = c >> 3, ch = (c & 7) ^ ((lr >> 1) & 7);
         const int r = PAIR ? (lr >> 6) * 32 + (lr & 31) : lr;
-        off[e] = static_cast<uint32_t>(min(r0 + r, last) - r0) * ld2 + ch * 16;
+        off[e] = static_cast<uint32_t>(min(r0 + r, last) - r0) * ldb + ch * 16;
       });
-      const int r = PERM ? acc_row(lane & 15) : lane & 15, x = (r >> 1) & 7;
-      static_for<2>([&](auto ks) EE_ALWAYS_INLINE {
-        rd[ks] = lds + (wrow + r) * 128 + (((decltype(ks)::value * 4 + (lane >> 4)) ^ x) << 4);
-      });
+      if constexpr (kB16) {
+        const int r = PERM ? acc_row(lane & 15) : lane & 15, x = (r >> 1) & 7;
+        static_for<2>([&](auto ks) EE_ALWAYS_INLINE {
+          rd[ks] = lds + (wrow + r) * 128 + (((decltype(ks)::value * 4 + (lane >> 4)) ^ x) << 4);
+        });
+      } else {
+        const int r = lane & 31, x = (r >> 1) & 7;
+        static_for<4>([&](auto g) EE_ALWAYS_INLINE {
+          rd[g] = lds + (wrow + r) * 128 + (((2 * (kw < 0 ? decltype(g)::value : kw) + (lane >> 5)) ^ x) << 4);
+        });
+      }
     } else {
       base = reinterpret_cast<const char *>(p + static_cast<int64_t>(kbeg) * O.ld + row0);
-      step = static_cast<int64_t>(ld2) * 64;
-      kr = tid >> 4;
+      step = static_cast<int64_t>(ldb) * KS;
+      kr = tid / KCH;
+      constexpr int V = 16 / sizeof(T);
       static_for<LOADS>([&](auto e) EE_ALWAYS_INLINE {
-        const int c = decltype(e)::value * THREADS + tid, k = c >> 4, ch = (c & 15) ^ swz(k);
-        off[e] = static_cast<uint32_t>(min(row0 + ch * 8, rows - 8) - row0) * 2;
+        const int c = decltype(e)::value * THREADS + tid, k = c / KCH, ch = (c % KCH) ^ swz(k);
+        off[e] = static_cast<uint32_t>(min(row0 + ch * V, rows - V) - row0) * sizeof(T);
       });
-      const int k = 8 * (lane >> 4) + ((lane >> 2) & 3), j = lane & 3;
-      const int m = PERM ? (j & 1) * 8 + (j >> 1) * 4 : 4 * j;
-      static_for<ROWS / 16>([&](auto i) EE_ALWAYS_INLINE {
-        const int row = (wrow + decltype(i)::value * 16 + m) & (ROWS - 1);  // (blocks past the wave's rows are not read)
-        rd[i] = lds + k * 256 + (((row >> 3) ^ swz(k)) << 4) + (row & 7) * 2;
-      });
+      if constexpr (kB16) {
+        const int k = 8 * (lane >> 4) + ((lane >> 2) & 3), j = lane & 3;
+        const int m = PERM ? (j & 1) * 8 + (j >> 1) * 4 : 4 * j;
+        static_for<ROWS / 16>([&](auto i) EE_ALWAYS_INLINE {
+          const int row = (wrow + decltype(i)::value * 16 + m) & (ROWS - 1);  // (blocks past the wave's rows are not read)
+          rd[i] = lds + k * KROW + (((row >> 3) ^ swz(k)) << 4) + (row & 7) * 2;
+        });
+      } else {
+        rd[0] = lds + (8 * (kw < 0 ? 0 : kw) + 4 * (lane >> 5)) * KROW + (wrow + (lane & 31)) * 4;
+      }
     }
   }
   // Stage t into LDS from lds_wave on (the wave's first chunk of the operand);
@@ -132,7 +152,7 @@ struct RingOperand {
     static_for<LOADS>([&](auto e) EE_ALWAYS_INLINE {
       constexpr int E = decltype(e)::value;
       uint32_t o = off[E];
-      if constexpr (!KM) o += __umul24(min(static_cast<int>(kr) + E * THREADS / 16, left - 1), ld2);
+      if constexpr (!KM) o += __umul24(min(static_cast<int>(kr) + E * KSTEP, left - 1), ldb);
       load_lds16(PAIR && ((E * THREADS / 8) >> 5) % 2 == 1 ? p + pair : p, o, lds_wave + E * THREADS * 16);
     });
   }
@@ -140,23 +160,39 @@ struct RingOperand {
   __device__ __forceinline__ void zero_tail(int left, int tid, char *lds) const {
     static_for<LOADS>([&](auto e) EE_ALWAYS_INLINE {
       constexpr int E = decltype(e)::value;
-      if (static_cast<int>(kr) + E * THREADS / 16 >= left)
+      if (static_cast<int>(kr) + E * KSTEP >= left)
         *reinterpret_cast<u32x4_t *>(lds + E * THREADS * 16 + tid * 16) = u32x4_t{0, 0, 0, 0};
     });
   }
-  // Fragments of NBLK 16-row blocks at the KS-th 32 values of K of the stage
-  // `stage` bytes from stage 0.
-  template <int KS, int NBLK>
+  // bf16: fragments of NBLK 16-row blocks at the KS-th 32 values of K of the
+  // stage `stage` bytes from stage 0.
+  template <int KSI, int NBLK>
   __device__ __forceinline__ void read(int stage, bf16x8_t (&f)[NBLK]) const {
     static_for<NBLK>([&](auto i) EE_ALWAYS_INLINE {
       constexpr int I = decltype(i)::value;
       if constexpr (KM) {
-        f[I] = *reinterpret_cast<const bf16x8_t *>(rd[KS] + stage + I * 2048);
+        f[I] = *reinterpret_cast<const bf16x8_t *>(rd[KSI] + stage + I * 2048);
       } else {
-        const char *p = rd[I] + stage + KS * 8192;
+        const char *p = rd[I] + stage + KSI * 8192;
         const s16x4_t both[2] = {__builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_t *)(p)),
                                  __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_t *)(p + 1024))};
         f[I] = __builtin_bit_cast(bf16x8_t, both);
+      }
+    });
+  }
+  // fp32: values K = 8 (kw + G) + 4 (lane / 32) + 0..3 of the lane's row in NBLK
+  // 32-row blocks.
+  template <int G, int NBLK>
+  __device__ __forceinline__ void read4(int stage, f32x4_t (&f)[NBLK]) const {
+    static_for<NBLK>([&](auto i) EE_ALWAYS_INLINE {
+      constexpr int I = decltype(i)::value;
+      if constexpr (KM) {
+        f[I] = *reinterpret_cast<const f32x4_t *>(rd[G] + stage + I * 4096);
+      } else {
+        static_for<4>([&](auto e) EE_ALWAYS_INLINE {
+          f[I][decltype(e)::value] =
+              *reinterpret_cast<const float *>(rd[0] + stage + (8 * G + decltype(e)::value) * KROW + I * 128);
+        });
       }
     });
   }
@@ -178,8 +214,8 @@ struct Ring {
   static constexpr int BM = BM_, BN = BN_, WM = WM_, WN = WN_, NS = NS_;
   static constexpr int WAVES_M = BM / WM, WAVES_N = BN / WN, THREADS = WAVES_M * WAVES_N * 64;
   static constexpr int STAGE_BYTES = (BM + BN) * 128;
-  using TA = RingOperand<AK, BM, THREADS, true, A_PAIR>;
-  using TB = RingOperand<BKM, BN, THREADS, false, B_PAIR>;
+  using TA = RingOperand<bf16_t, AK, BM, THREADS, true, A_PAIR>;
+  using TB = RingOperand<bf16_t, BKM, BN, THREADS, false, B_PAIR>;
   static constexpr int LOADS = TA::LOADS + TB::LOADS;
   using Acc = f32x4_t[WM / 16][WN / 16];
   static_assert((NS - 2) * LOADS <= 63, "loads in flight past the waited-for stage");
@@ -268,6 +304,99 @@ struct Ring {
       }
     });
     phase_barrier();
+  }
+};
+
+// The same ring for fp32 operands, 32 values of K a stage,
+// v_mfma_f32_32x32x2_f32: a BM x BN tile on waves of 64 x 64.  KW = 4: the four
+// waves of a 64 x 64 tile take 8 values of K each and their sums are added up,
+// in order, in the first wave (the others' sums pass through LDS, 16 KB each).
+template <int BM_, int BN_, int KW_, int NS_, bool AK, bool BKM, bool B_PAIR>
+struct RingF32 {
+  static constexpr int BM = BM_, BN = BN_, KW = KW_, NS = NS_;
+  static constexpr int WAVES_N = BN / 64, THREADS = BM / 64 * WAVES_N * KW * 64;
+  static constexpr int STAGE_BYTES = (BM + BN) * 128;
+  using TA = RingOperand<float, AK, BM, THREADS, false, false>;
+  using TB = RingOperand<float, BKM, BN, THREADS, false, B_PAIR>;
+  static constexpr int LOADS = TA::LOADS + TB::LOADS;
+  static_assert(KW == 1 || (KW == 4 && BM == 64 && BN == 64 && 3 * 16384 <= NS * STAGE_BYTES), "one 64 x 64 tile");
+
+  // As Ring::run; with KW = 4 acc is whole in wave 0 only.
+  __device__ __forceinline__ static void run(const Operand &A, int m0, int M, const Operand &B, int n0, int N, int kbeg,
+                                             int K, int tid, char *smem, f32x16_t (&acc)[2][2]) {
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int nk = (K + 31) / 32, kw = KW == 4 ? wave : -1;
+    TA ta;
+    TB tb;
+    ta.init(A, m0, M, kbeg, tid, KW == 4 ? 0 : wave / WAVES_N * 64, lane, smem, kw);
+    tb.init(B, n0, N, kbeg, tid, KW == 4 ? 0 : wave % WAVES_N * 64, lane, smem + TA::BYTES, kw);
+    const uint32_t lds_wave =
+        static_cast<uint32_t>(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) char *)smem)) + wave * 1024;
+    auto load = [&](int t, int buf) EE_ALWAYS_INLINE {
+      ta.load(t, K - t * 32, lds_wave + buf * STAGE_BYTES);
+      tb.load(t, K - t * 32, lds_wave + buf * STAGE_BYTES + TA::BYTES);
+    };
+    static_for<2>([&](auto i) EE_ALWAYS_INLINE {
+      static_for<2>([&](auto j) EE_ALWAYS_INLINE {
+        static_for<16>([&](auto v) EE_ALWAYS_INLINE { acc[i][j][decltype(v)::value] = 0.0f; });
+      });
+    });
+    static_for<NS - 1>([&](auto t) EE_ALWAYS_INLINE {
+      if (decltype(t)::value < nk) load(decltype(t)::value, decltype(t)::value);
+    });
+    int cur = 0;  // buffer of stage t
+    for (int t = 0; t < nk; ++t) {
+      const int later = min(nk - 1 - t, NS - 2);
+      static_for<NS - 1>([&](auto l) EE_ALWAYS_INLINE {
+        if (later == decltype(l)::value) wait_vm<decltype(l)::value * LOADS>();
+      });
+      if constexpr (!AK) {
+        if (t == nk - 1 && K % 32 != 0) {  // zero A's k-rows past K, each thread the chunks it loaded itself
+          ta.zero_tail(K - t * 32, tid, smem + cur * STAGE_BYTES);
+          wait_lgkm();
+        }
+      }
+      phase_barrier();
+      if (t + NS - 1 < nk) load(t + NS - 1, cur == 0 ? NS - 1 : cur - 1);  // over stage t - 1, which every wave has read
+      const int stage = cur * STAGE_BYTES;
+      static_for<KW == 4 ? 1 : 4>([&](auto g) EE_ALWAYS_INLINE {
+        f32x4_t fa[2], fb[2];
+        ta.template read4<decltype(g)::value>(stage, fa);
+        tb.template read4<decltype(g)::value>(stage, fb);
+        static_for<4>([&](auto e) EE_ALWAYS_INLINE {
+          static_for<2>([&](auto i) EE_ALWAYS_INLINE {
+            static_for<2>([&](auto j) EE_ALWAYS_INLINE {
+              constexpr int E = decltype(e)::value;
+              acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[i][E], fb[j][E], acc[i][j], 0, 0, 0);
+            });
+          });
+        });
+      });
+      wait_lgkm();
+      cur = cur == NS - 1 ? 0 : cur + 1;
+    }
+    phase_barrier();
+    if constexpr (KW == 4) {
+      // [wave - 1][block and quarter][lane] of 16 bytes
+      f32x4_t *part = reinterpret_cast<f32x4_t *>(smem);
+      if (wave > 0) {
+        static_for<16>([&](auto q) EE_ALWAYS_INLINE {
+          constexpr int Q = decltype(q)::value, I = Q / 8, J = Q / 4 % 2, E = Q % 4 * 4;
+          part[((wave - 1) * 16 + Q) * 64 + lane] =
+              f32x4_t{acc[I][J][E], acc[I][J][E + 1], acc[I][J][E + 2], acc[I][J][E + 3]};
+        });
+      }
+      __syncthreads();
+      if (wave == 0) {
+        static_for<16>([&](auto q) EE_ALWAYS_INLINE {
+          constexpr int Q = decltype(q)::value, I = Q / 8, J = Q / 4 % 2, E = Q % 4 * 4;
+          static_for<3>([&](auto w) EE_ALWAYS_INLINE {
+            const f32x4_t v = part[(decltype(w)::value * 16 + Q) * 64 + lane];
+            static_for<4>([&](auto e) EE_ALWAYS_INLINE { acc[I][J][E + decltype(e)::value] += v[decltype(e)::value]; });
+          });
+        });
+      }
+    }
   }
 };
 

@@ -37,6 +37,40 @@ def test_pipeline_edges(name, kind, n, h, v, inter):
     compare_full(s, b, case=name)
 
 
+SMALL_TILE_CASES = [
+    # bf16 on 128 x 128 tiles: one stage and ragged tails; both operands
+    # MN-major with a K tail (dZ, dW_down); the split tail of dZ
+    ("mid_one_stage", W.EXIT_NORM, 130, 64, 300, 0, "bf16"),
+    ("mid_mlp_tails", W.EXIT_MLP, 333, 320, 1111, 448, "bf16"),
+    ("mid_split", W.EXIT_MLP, 700, 256, 2100, 1216, "bf16"),
+    # fp32: 64 x 64 tiles with waves that share K (K of one stage, K tails, the
+    # split products); 128 x 128 tiles K-major, with an interleaved pair, and
+    # MN-major with a K tail
+    ("f32_small", W.EXIT_NORM, 65, 64, 129, 0, "f32"),
+    ("f32_small_mlp", W.EXIT_MLP, 100, 192, 203, 320, "f32"),
+    ("f32_split", W.EXIT_MLP, 150, 128, 1100, 576, "f32"),
+    ("f32_big_logits", W.EXIT_NORM, 100, 64, 32700, 0, "f32"),
+    ("f32_big_gate_up", W.EXIT_MLP, 500, 64, 100, 4096, "f32"),
+    ("f32_big_dz", W.EXIT_MLP, 4000, 1024, 100, 64, "f32"),
+]
+
+
+@pytest.mark.parametrize("name,kind,n,h,v,inter,dtype", SMALL_TILE_CASES, ids=[c[0] for c in SMALL_TILE_CASES])
+def test_tile_choice_edges(name, kind, n, h, v, inter, dtype):
+    from paper_2402_00518_amd.session import Session
+    say(f"case: {name} N={n} h={h} V={v} I={inter} {dtype}")
+    b = small(kind, n, h, v, inter, dtype, seed=10, name=name)
+    s = Session.from_batch(b)
+    s.ws.fill_(0xFF)
+    s.step()
+    torch.cuda.synchronize()
+    s.check_device_error()
+    if dtype == "f32":
+        compare_full(s, b, loss_rtol=1e-5, grad_rtol=1e-4, case=name)
+    else:
+        compare_full(s, b, case=name)
+
+
 @pytest.mark.parametrize("kind,n,inter", [(W.EXIT_NORM, 70, 0), (W.EXIT_NORM, 513, 0), (W.EXIT_MLP, 150, 192)],
                          ids=["norm_70", "norm_513", "mlp_150"])
 def test_f32_padding_is_written(kind, n, inter):

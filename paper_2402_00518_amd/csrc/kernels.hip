@@ -670,17 +670,17 @@ __global__ __launch_bounds__(512) void ce_reduce_kernel(CeReduceArgs a) {
 // vocab tile (once per 64-row softmax slice).
 constexpr int kSeedRows = 128;
 // One block of the seed: vocab rows bx * kSeedRows .., tokens by * 2048 ..
-template <typename T>
+template <typename T, int ROWS = kSeedRows>
 __device__ __forceinline__ void seed_block(int bx, int by, T *P, const float *part_m, const float *lse,
                                            const float *sn, const int32_t *targets, int n, int ldn, int vocab,
                                            int vtile, float *gsum_part, const float *coef = nullptr) {
   // coef != NULL: only the row sums of G = diag(coef) P (the unshifted
   // form's G, with P's target entries already shifted); P is not written.
   const bool sums_only = coef != nullptr;
-  __shared__ float red[kSeedRows][4];
+  __shared__ float red[ROWS][4];
   const int c0 = by * 2048 + threadIdx.x * 8;
   if (gsum_part == nullptr && c0 >= ldn) return;
-  const int vb = bx * kSeedRows;
+  const int vb = bx * ROWS;
   float cf[8], s[8], lz[8];
   int yy[8];
   bool ok[8];
@@ -698,7 +698,7 @@ __device__ __forceinline__ void seed_block(int bx, int by, T *P, const float *pa
   constexpr int VEC = 8 * sizeof(T) / 16;  // 16-byte vectors per 8 values
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
 #pragma unroll
-  for (int b = 0; b < kSeedRows / 16; ++b) {
+  for (int b = 0; b < ROWS / 16; ++b) {
     const int v0 = vb + 16 * b;
     const int rows = min(16, vocab - v0);
     if (rows <= 0) break;  // uniform: past the vocabulary
@@ -753,7 +753,7 @@ __device__ __forceinline__ void seed_block(int bx, int by, T *P, const float *pa
   }
   if (gsum_part == nullptr) return;
   __syncthreads();
-  const int rows_all = min(kSeedRows, vocab - vb);
+  const int rows_all = min(ROWS, vocab - vb);
   if (static_cast<int>(threadIdx.x) < rows_all)
     gsum_part[static_cast<int64_t>(by) * vocab + vb + threadIdx.x] =
         ((red[threadIdx.x][0] + red[threadIdx.x][1]) + red[threadIdx.x][2]) + red[threadIdx.x][3];
@@ -1054,6 +1054,10 @@ hipError_t launch_seed_or_scale(bool f32, void *P, void *x_hat_t, const float *p
   return hipGetLastError();
 }
 
+// (Fewer rows a block than the seed, whose coefficients cost it more per block:
+// a chunk of 2048 tokens and 32003 rows are 251 blocks of 128 rows, one a CU,
+// and 1001 of 32: 40 against 29 us.)
+constexpr int kGsumRows = 32;
 // Row sums of G = diag(coef) P' per 2048-token chunk (the seed's partials),
 // for the bias gradient of an exit in the unshifted form, after the operand
 // scale has shifted P's target entries; nothing if the exit fell back to
@@ -1062,7 +1066,7 @@ template <typename T>
 __global__ __launch_bounds__(256) void gsum_unshifted_kernel(const T *P, const float *coef, int n, int ldn, int vocab,
                                                              const int *fallback, float *gsum_part) {
   if (*fallback != 0) return;  // the same word for every thread
-  seed_block<T>(blockIdx.x, blockIdx.y, const_cast<T *>(P), nullptr, nullptr, nullptr, nullptr, n, ldn, vocab, 1,
+  seed_block<T, kGsumRows>(blockIdx.x, blockIdx.y, const_cast<T *>(P), nullptr, nullptr, nullptr, nullptr, n, ldn, vocab, 1,
                 gsum_part, coef);
 }
 
@@ -1070,7 +1074,7 @@ hipError_t launch_gsum_unshifted(bool f32, const void *P, const float *coef, int
                                  const int *fallback, float *gsum_part, hipStream_t stream) {
   if (n <= 0 || vocab <= 0) return hipSuccess;
   if (ldn % 8 != 0 || coef == nullptr || fallback == nullptr || gsum_part == nullptr) return hipErrorInvalidValue;
-  const dim3 grid(cdiv(vocab, kSeedRows), seed_chunks(ldn));
+  const dim3 grid(cdiv(vocab, kGsumRows), seed_chunks(ldn));
   EE_DISPATCH(f32, hipLaunchKernelGGL(gsum_unshifted_kernel<T>, grid, dim3(256), 0, stream, static_cast<const T *>(P),
                                       coef, n, ldn, vocab, fallback, gsum_part));
   return hipGetLastError();

@@ -619,7 +619,7 @@ template <> struct GatePair<float> {
 
 // Gate and up projections as one product, with the SwiGLU product.  The B
 // operand interleaves the rows of W_gate and W_up in blocks of 32
-// (KMajorPairLoader; C has 2F columns for F features), so a lane's two
+// (kPairB; C has 2F columns for F features), so a lane's two
 // column blocks hold H_g and H_u of the same tokens and feature
 // f = n0 / 2 + wave_n * 32 + lane % 32.  Stores, token-major, the pair
 // (H_g, H_u) at Hgu[n][f] and A = silu(H_g) * H_u at A[n][f], with H_g

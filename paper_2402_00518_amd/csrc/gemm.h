@@ -56,7 +56,7 @@ struct TileCfg {
 // 1.5x the MFMA work per byte read from LDS of the small tile, and a second
 // wave per SIMD to issue while the other waits.
 using CfgBig = TileCfg<256, 256, 128, 64, 1>;
-// 128 x 128 tile, 64 x 64 per wave, a ring of 4 stages: bf16 products with too
+// 128 x 128 tile, 64 x 64 per wave, a ring of 2 stages: bf16 products with too
 // few 256 x 256 tiles to fill the chip.
 using CfgMid = TileCfg<128, 128, 64, 64, 2, 2>;
 // fp32: 128 x 128 on 4 waves of 64 x 64, or 64 x 64 on 4 waves that share K.

@@ -1054,29 +1054,37 @@ hipError_t launch_seed_or_scale(bool f32, void *P, void *x_hat_t, const float *p
   return hipGetLastError();
 }
 
-// (Fewer rows a block than the seed, whose coefficients cost it more per block:
-// a chunk of 2048 tokens and 32003 rows are 251 blocks of 128 rows, one a CU,
-// and 1001 of 32: 40 against 29 us.)
-constexpr int kGsumRows = 32;
+// 32 rows a block where the seed's 128 give fewer than 448 blocks (2048 tokens
+// and 32003 rows: 251 blocks of 128 rows, one a CU, 40 us, 1001 of 32 29 us),
+// else 128, as each block loads its tokens' coefficients once (4096 tokens and
+// 32000 rows: 500 blocks of 128 59 us, 2000 of 32 63.5 us).
+constexpr int kGsumRowsFew = 32;
 // Row sums of G = diag(coef) P' per 2048-token chunk (the seed's partials),
 // for the bias gradient of an exit in the unshifted form, after the operand
 // scale has shifted P's target entries; nothing if the exit fell back to
 // the shifted form, whose seed wrote them.
-template <typename T>
+template <typename T, int ROWS>
 __global__ __launch_bounds__(256) void gsum_unshifted_kernel(const T *P, const float *coef, int n, int ldn, int vocab,
                                                              const int *fallback, float *gsum_part) {
   if (*fallback != 0) return;  // the same word for every thread
-  seed_block<T, kGsumRows>(blockIdx.x, blockIdx.y, const_cast<T *>(P), nullptr, nullptr, nullptr, nullptr, n, ldn, vocab, 1,
-                gsum_part, coef);
+  seed_block<T, ROWS>(blockIdx.x, blockIdx.y, const_cast<T *>(P), nullptr, nullptr, nullptr, nullptr, n, ldn, vocab, 1,
+                      gsum_part, coef);
 }
 
 hipError_t launch_gsum_unshifted(bool f32, const void *P, const float *coef, int n, int ldn, int vocab,
                                  const int *fallback, float *gsum_part, hipStream_t stream) {
   if (n <= 0 || vocab <= 0) return hipSuccess;
   if (ldn % 8 != 0 || coef == nullptr || fallback == nullptr || gsum_part == nullptr) return hipErrorInvalidValue;
-  const dim3 grid(cdiv(vocab, kGsumRows), seed_chunks(ldn));
-  EE_DISPATCH(f32, hipLaunchKernelGGL(gsum_unshifted_kernel<T>, grid, dim3(256), 0, stream, static_cast<const T *>(P),
-                                      coef, n, ldn, vocab, fallback, gsum_part));
+  auto go = [&](auto rows) {
+    constexpr int ROWS = decltype(rows)::value;
+    const dim3 grid(cdiv(vocab, ROWS), seed_chunks(ldn));
+    EE_DISPATCH(f32, hipLaunchKernelGGL((gsum_unshifted_kernel<T, ROWS>), grid, dim3(256), 0, stream,
+                                        static_cast<const T *>(P), coef, n, ldn, vocab, fallback, gsum_part));
+  };
+  if (static_cast<int64_t>(cdiv(vocab, kSeedRows)) * seed_chunks(ldn) < 448)
+    go(std::integral_constant<int, kGsumRowsFew>{});
+  else
+    go(std::integral_constant<int, kSeedRows>{});
   return hipGetLastError();
 }
 

@@ -4,9 +4,10 @@
 // At decode the products are skinny, C[r][j] = sum_k W[r][k] Z[j][k] with a
 // weight W of R rows and B token rows Z, bound by streaming W from HBM once.
 //
-// bf16: ring_kernel, W and Z through LDS (see launch_ring).
+// bf16: ring_kernel, W and Z through LDS (see launch_ring); skinny_kernel where
+// W has few rows (see decode_skinny_logits).
 //
-// fp32: skinny_kernel, 32 tokens a pass.  A block owns 32 rows of W (64 for a
+// fp32, and those: skinny_kernel, 32 tokens a pass.  A block owns 32 rows of W (64 for a
 // wide W past 8 token rows, so that each token fragment serves two row groups
 // and the token rows' share of the loads halves); each of its waves takes a
 // share of K and reads its rows straight into MFMA A fragments (16 bytes of K
@@ -46,27 +47,37 @@ __host__ __device__ constexpr int dec_waves(int row_blocks) {
 }
 constexpr int kDecGroup = 12;   // fragment loads per operand per lane in flight (8 and 16 measured slower)
 
-// A 16-byte load holds 4 values of K; four MFMAs of K = 2 (lane halves hold K
-// offsets 0-3 and 4-7 of the same 8, in the same order for A and B).
-constexpr int kDecKPerLoad = 8;  // values of K covered by one load across the wave
-__device__ __forceinline__ void dec_mma(const u32x4_t &a, const u32x4_t &b, f32x16_t &acc) {
-  static_for<4>([&](auto e) EE_ALWAYS_INLINE {
-    constexpr int E = decltype(e)::value;
-    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a[E]), __uint_as_float(b[E]), acc, 0, 0, 0);
-  });
-}
+template <typename T> struct DecFrag;
+// bf16: a 16-byte load holds 8 values of K; one MFMA consumes 16 (two lane halves).
+template <> struct DecFrag<bf16_t> {
+  static constexpr int K_PER_LOAD = 16;  // values of K covered by one load across the wave
+  __device__ __forceinline__ static void mma(const u32x4_t &a, const u32x4_t &b, f32x16_t &acc) {
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b),
+                                                  acc, 0, 0, 0);
+  }
+};
+// fp32: a 16-byte load holds 4 values of K; four MFMAs of K = 2 (lane halves
+// hold K offsets 0-3 and 4-7 of the same 8, in the same order for A and B).
+template <> struct DecFrag<float> {
+  static constexpr int K_PER_LOAD = 8;
+  __device__ __forceinline__ static void mma(const u32x4_t &a, const u32x4_t &b, f32x16_t &acc) {
+    static_for<4>([&](auto e) EE_ALWAYS_INLINE {
+      constexpr int E = decltype(e)::value;
+      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a[E]), __uint_as_float(b[E]), acc, 0, 0, 0);
+    });
+  }
+};
 
 // acc[v] of lane l: row r0 + (v/4)*8 + (l/32)*4 + v%4, token j0 + l%32.
 __device__ __forceinline__ int dec_row(int r0, int lane, int v) {
   return r0 + (v >> 2) * 8 + (lane >> 5) * 4 + (v & 3);
 }
 
-template <class Epi, int kDecWaves, int RG>
-__global__ __launch_bounds__(64 * kDecWaves) void skinny_kernel(const float *__restrict__ W, int64_t ldw, int R,
-                                                                const float *__restrict__ Z, int64_t ldz, int B, int K,
+template <typename T, class Epi, int kDecWaves, int RG>
+__global__ __launch_bounds__(64 * kDecWaves) void skinny_kernel(const T *__restrict__ W, int64_t ldw, int R,
+                                                                const T *__restrict__ Z, int64_t ldz, int B, int K,
                                                                 typename Epi::Params ep) {
-  using T = float;
-  constexpr int KL = kDecKPerLoad;
+  constexpr int KL = DecFrag<T>::K_PER_LOAD;
   constexpr int PER_LOAD = 16 / sizeof(T);  // elements of one 16-byte load
   __shared__ f32x16_t red[kDecWaves - 1][64];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -109,7 +120,7 @@ __global__ __launch_bounds__(64 * kDecWaves) void skinny_kernel(const float *__r
     __builtin_amdgcn_sched_barrier(0);
     static_for<NQ>([&](auto q) EE_ALWAYS_INLINE {
       static_for<RG>([&](auto g) EE_ALWAYS_INLINE {
-        dec_mma(a[decltype(g)::value][decltype(q)::value], b[decltype(q)::value], acc[decltype(g)::value]);
+        DecFrag<T>::mma(a[decltype(g)::value][decltype(q)::value], b[decltype(q)::value], acc[decltype(g)::value]);
       });
     });
   };
@@ -483,8 +494,8 @@ hipError_t launch_ring(Operand W, int R, Operand Z, int B, int K, int splits, co
   return launch_ring_cfg<Epi, 128, 128, 64, 4, 1, PAIR>(W, R, Z, B, K, splits, ep, stream);
 }
 
-template <class Epi, int RG>
-hipError_t launch_skinny_rg(const float *w, int64_t ldw, int R, const float *z, int64_t ldz, int B, int K,
+template <typename T, class Epi, int RG>
+hipError_t launch_skinny_rg(const T *w, int64_t ldw, int R, const T *z, int64_t ldz, int B, int K,
                             const typename Epi::Params &ep, hipStream_t stream) {
   const int row_blocks = (R + kDecRows * RG - 1) / (kDecRows * RG);
   const dim3 grid(static_cast<unsigned>(row_blocks), static_cast<unsigned>((B + kDecTokens - 1) / kDecTokens));
@@ -492,14 +503,14 @@ hipError_t launch_skinny_rg(const float *w, int64_t ldw, int R, const float *z, 
   const int waves = RG > 1 ? std::min(dec_waves(row_blocks), 8) : dec_waves(row_blocks);
   switch (waves) {
     case 4:
-      hipLaunchKernelGGL((skinny_kernel<Epi, 4, RG>), grid, dim3(64 * 4), 0, stream, w, ldw, R, z, ldz, B, K, ep);
+      hipLaunchKernelGGL((skinny_kernel<T, Epi, 4, RG>), grid, dim3(64 * 4), 0, stream, w, ldw, R, z, ldz, B, K, ep);
       break;
     case 8:
-      hipLaunchKernelGGL((skinny_kernel<Epi, 8, RG>), grid, dim3(64 * 8), 0, stream, w, ldw, R, z, ldz, B, K, ep);
+      hipLaunchKernelGGL((skinny_kernel<T, Epi, 8, RG>), grid, dim3(64 * 8), 0, stream, w, ldw, R, z, ldz, B, K, ep);
       break;
     default:
       if constexpr (RG == 1)
-        hipLaunchKernelGGL((skinny_kernel<Epi, kDecWavesMax, RG>), grid, dim3(64 * kDecWavesMax), 0, stream, w, ldw,
+        hipLaunchKernelGGL((skinny_kernel<T, Epi, kDecWavesMax, RG>), grid, dim3(64 * kDecWavesMax), 0, stream, w, ldw,
                            R, z, ldz, B, K, ep);
   }
   return hipGetLastError();
@@ -509,18 +520,63 @@ hipError_t launch_skinny_rg(const float *w, int64_t ldw, int R, const float *z, 
 // 32-row groups per token fragment, halving the token rows' share of the
 // loads (at 8 waves a block: measured 11% faster at 32 tokens for 13824 and
 // 32000 rows; with 5120 rows the 80 blocks kept too few loads in flight).
-template <class Epi>
+template <typename T, class Epi>
 hipError_t launch_skinny(const void *W, int64_t ldw, int R, const void *Z, int64_t ldz, int B, int K,
                          const typename Epi::Params &ep, hipStream_t stream) {
   if (R <= 0 || B <= 0) return hipSuccess;
-  if (K % (4 * kDecKPerLoad) != 0) return hipErrorInvalidValue;
-  const float *w = static_cast<const float *>(W);
-  const float *z = static_cast<const float *>(Z);
-  if (B > 8 && R >= 12288) return launch_skinny_rg<Epi, 2>(w, ldw, R, z, ldz, B, K, ep, stream);
-  return launch_skinny_rg<Epi, 1>(w, ldw, R, z, ldz, B, K, ep, stream);
+  if (K % (4 * DecFrag<T>::K_PER_LOAD) != 0) return hipErrorInvalidValue;
+  const T *w = static_cast<const T *>(W);
+  const T *z = static_cast<const T *>(Z);
+  if (B > 8 && R >= 12288) return launch_skinny_rg<T, Epi, 2>(w, ldw, R, z, ldz, B, K, ep, stream);
+  return launch_skinny_rg<T, Epi, 1>(w, ldw, R, z, ldz, B, K, ep, stream);
 }
 
 }  // namespace
+
+// Which bf16 products skinny_kernel takes.  It has 32 rows of W a block and up
+// to 16 waves that share K, where a block of the ring has 128 rows (64 for
+// the split down projection) and two or four waves that walk all of K: few
+// rows of W leave the ring a latency chain on a few CUs.  But skinny_kernel
+// reads W once for every 32 tokens, so it loses past one round of 16 waves a
+// CU (two rounds past 64 tokens, where the ring has a 128-token block).  us a
+// call, ring against skinny, W from memory (Embedding exit, h 4096):
+//   1 token: V 2000 36.5 against 17.1, 8192 36.8/20.1, 16384 38.3/29.7, 24000
+//   42.9/41.7;
+//   32 tokens: 2000 37.8/24.7, 8192 38.9/26.1, 10000 39.1/40.0, 20000 45.6/71.2;
+//   64 tokens: 4096 39.9/25.6, 6000 40.6/42.7 (48 tokens 40.0/38.9, and with h
+//   2048 23.7/24.6); 128: 4096 53.2/42.4, 6000 54.1/61.0; 256: 2000 52.8/42.8,
+//   3000 53.2/59.8; 96 tokens, V 8192: 53.9/53.5, h 1024 22.4/20.0.
+// Past a block a CU (8192 rows) it depends on the tokens' share of the loads (h
+// 5120, V 10000: 16 tokens 44.0/44.6, 32 46.3/54.3), on the stride of the rows (a
+// multiple of 8 KB, or of 4 KB with long rows, favours waves spread over K: 24
+// tokens, V 14000, h 4096 39.9/38.7, h 5120 47.4/49.2; the ring takes no parts at
+// an odd multiple of 4 KB: h 2048, V 48000, 8 tokens 51.1/45.4) and on whether the
+// ring's 128-row blocks are a few more than the CUs, so that some CUs take two
+// (h 4096, 1 token, ring time over skinny's: V 28000 0.95, 33000 1.16, 38111
+// 1.17, 48000 1.06, 58000 0.97; 8 tokens 0.88, 1.13, 1.11, 1.02, 0.91).
+constexpr int kWavesRound = 16 * 256;  // 16 waves a CU
+bool decode_skinny_logits(int rows, int n, int k) {
+  const int64_t rb = cdiv64(rows, kDecRows), passes = cdiv64(n, kDecTokens), waves = rb * passes * dec_waves(rb);
+  if (n > 64) return rb < 256 ? waves <= 2 * kWavesRound : (k <= 2048 && 2 * waves <= 3 * kWavesRound);
+  if (n > 32) return (n <= 48 && k >= 4096 && rb <= 192) || (rb <= 256 && waves <= kWavesRound);
+  if (rb <= 256 || (rb < 384 && n <= 16)) return true;
+  const int stride = k * 2;
+  if (rb <= 512) return n <= 8 || (n <= 24 && k >= 4096 && stride % 4096 == 0);
+  if (n > 8) return false;
+  if (k <= 512 || stride % kCampBytes == kCampBytes / 2 || (n <= 4 && k <= 1536)) return true;
+  return rb > 1024 && (rb <= 1216 || (rb <= 1536 && n <= 4 && k < 8192));
+}
+// The ring splits K here and keeps up except where K is short (us a call of the
+// whole MLP exit, V 8000, ring against skinny: h 512, I 1344: 1 token 31/30, 250
+// tokens 49/43; h = I = 4096: 1 token 92/89; h 2048, I 5504: 1 token 58/59) and,
+// past 64 tokens, skinny_kernel takes one round (h = I = 2048: 128 tokens 77/73,
+// 250 tokens 80/83).  From 9 to 64 tokens the two are within 2 us.
+bool decode_skinny_down(int rows, int n, int k) {
+  const bool short_k = 4 * static_cast<int64_t>(k) <= 11 * static_cast<int64_t>(rows);
+  if (n <= 8) return k <= rows || (rows <= 512 && short_k);
+  const int64_t rb = cdiv64(rows, kDecRows), passes = cdiv64(n, kDecTokens);
+  return n > 64 && (k <= rows || (rows <= 1024 && short_k)) && rb * passes * dec_waves(rb) <= kWavesRound;
+}
 
 int decode_tiles(int rows) { return (rows + kDecRows - 1) / kDecRows; }
 
@@ -531,16 +587,17 @@ hipError_t decode_gate_up(bool f32, const void *w_gate, const void *w_up, int ro
     return launch_ring<DecGateUp, true>(Operand{w_gate, k, pair}, rows, Operand{z, k}, n, k, 1,
                                         {static_cast<bf16_t *>(act), rows}, stream);
   }
-  const hipError_t e = launch_skinny<DecStore>(w_gate, k, rows, z, k, n, k, {static_cast<float *>(hg), rows}, stream);
+  const hipError_t e =
+      launch_skinny<float, DecStore>(w_gate, k, rows, z, k, n, k, {static_cast<float *>(hg), rows}, stream);
   if (e != hipSuccess) return e;
-  return launch_skinny<DecSwiGLU>(w_up, k, rows, z, k, n, k,
-                                  {static_cast<const float *>(hg), static_cast<float *>(act), rows}, stream);
+  return launch_skinny<float, DecSwiGLU>(w_up, k, rows, z, k, n, k,
+                                         {static_cast<const float *>(hg), static_cast<float *>(act), rows}, stream);
 }
 
 // Slices of the down projection's K: enough for two 64-row blocks a CU (two
 // 128-row blocks past 128 tokens), at most `most`, and 512 values of K each.
 int decode_residual_splits(bool f32, int rows, int n, int k, int most) {
-  if (f32) return 1;
+  if (f32 || decode_skinny_down(rows, n, k)) return 1;
   const int64_t bm = n <= 128 ? 64 : 128, blocks = (rows + bm - 1) / bm * ((n + 127) / 128);
   const int s = static_cast<int>(std::max<int64_t>(1, std::min<int64_t>({most, 512 / blocks, k / 512})));
   return cdiv64(k / 64, cdiv64(k / 64, s));  // slices of whole stages, none empty
@@ -548,10 +605,11 @@ int decode_residual_splits(bool f32, int rows, int n, int k, int most) {
 
 hipError_t decode_residual(bool f32, const void *w, int rows, const void *z, int n, int k, const void *x,
                            float *y, int splits, float *extra, hipStream_t stream) {
-  if (splits < 1 || (splits > 1 && (f32 || extra == nullptr))) return hipErrorInvalidValue;
-  if (f32)
-    return launch_skinny<DecResidual<float>>(w, k, rows, z, k, n, k, {static_cast<const float *>(x), y, rows, nullptr, 0},
-                                             stream);
+  const bool skinny = f32 || decode_skinny_down(rows, n, k);
+  if (splits < 1 || (splits > 1 && (skinny || extra == nullptr))) return hipErrorInvalidValue;
+  if (skinny)
+    EE_DISPATCH(f32, return (launch_skinny<T, DecResidual<T>>(w, k, rows, z, k, n, k,
+                                                              {static_cast<const T *>(x), y, rows, nullptr, 0}, stream)));
   return launch_ring<DecResidual<bf16_t>, false>(
       Operand{w, k}, rows, Operand{z, k}, n, k, splits,
       {static_cast<const bf16_t *>(x), y, rows, extra, static_cast<int64_t>(n) * rows}, stream);
@@ -560,7 +618,8 @@ hipError_t decode_residual(bool f32, const void *w, int rows, const void *z, int
 hipError_t decode_logits(bool f32, const void *w_out, int vocab, const void *z, int n, int h, float *part_m,
                          float *part_l, int32_t *part_arg, hipStream_t stream) {
   const DecLogits::Params ep{part_m, part_l, part_arg, n};
-  if (f32) return launch_skinny<DecLogits>(w_out, h, vocab, z, h, n, h, ep, stream);
+  if (f32 || decode_skinny_logits(vocab, n, h))
+    EE_DISPATCH(f32, return (launch_skinny<T, DecLogits>(w_out, h, vocab, z, h, n, h, ep, stream)));
   return launch_ring<DecLogits, false>(Operand{w_out, h}, vocab, Operand{z, h}, n, h, 1, ep, stream);
 }
 

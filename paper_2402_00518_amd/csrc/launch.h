@@ -215,6 +215,10 @@ struct AdamBatchArgs {
 // (any n) against a weight of `rows` K-contiguous rows, K a
 // multiple of 64.  Outputs are token-major, [n][rows].
 int decode_tiles(int rows);  // partial rows per token of decode_logits
+// bf16 products of `rows` rows of W and n tokens, sums of length k, that take
+// the 32-row blocks of fp32 products rather than the LDS ring.
+bool decode_skinny_logits(int rows, int n, int k);
+bool decode_skinny_down(int rows, int n, int k);
 // Gate and up projections with the SwiGLU product, act[n][rows] (fp32: two
 // launches, the gate's product through hg[n][rows]; bf16: one, hg unused).
 hipError_t decode_gate_up(bool f32, const void *w_gate, const void *w_up, int rows, const void *z, int n, int k,

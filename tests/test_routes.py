@@ -1,0 +1,28 @@
+"""The shape rules that choose a kernel, at points where both sides were measured."""
+
+import pytest
+
+from routes import skinny_down, skinny_logits
+
+# (vocab, tokens, hidden): 32-row blocks measured faster than the ring, and slower
+FEW = [(2000, 1, 512), (2000, 1, 8192), (8192, 32, 4096), (10000, 16, 4096), (16384, 8, 8192), (16384, 24, 4096),
+       (4096, 64, 2048), (2000, 128, 8192), (4096, 128, 1024), (3000, 129, 4096), (2000, 256, 512), (1000, 512, 2048),
+       (48000, 8, 2048), (6000, 48, 8192), (8192, 96, 1024), (33000, 8, 4096), (48000, 4, 5120)]
+MANY = [(32000, 1, 4096), (32000, 8, 4096), (32000, 1, 5120), (32000, 64, 8192), (12000, 32, 5120), (20000, 16, 2048),
+        (6000, 64, 4096), (10000, 33, 1024), (6000, 128, 4096), (8192, 128, 4096), (3000, 256, 4096), (2000, 500, 4096),
+        (32000, 230, 5120), (64000, 500, 8192), (58000, 1, 4096), (33000, 16, 4096)]
+
+
+@pytest.mark.parametrize("vocab,n,h", FEW)
+def test_few_rows_take_small_blocks(vocab, n, h):
+    assert skinny_logits(vocab, n, h)
+
+
+@pytest.mark.parametrize("vocab,n,h", MANY)
+def test_many_rows_take_the_ring(vocab, n, h):
+    assert not skinny_logits(vocab, n, h)
+
+
+def test_down_projection():
+    assert skinny_down(512, 1, 1344) and skinny_down(1024, 250, 1024) and skinny_down(2048, 128, 2048)
+    assert not skinny_down(2048, 250, 2048) and not skinny_down(5120, 8, 13824) and not skinny_down(2048, 1, 5504)

@@ -142,7 +142,10 @@ typedef struct ee_exit_grads {
 
 /* Bytes of device workspace needed to run the given exits over n_tokens
  * rows, forward and backward.  One workspace serves every exit of
- * ee_multi_exit_step (they run one after another on the stream).  Returns 0
+ * ee_multi_exit_step (they run one after another on the stream).  More tokens
+ * never need less, except with bf16 MLP exits, whose split products hold up to
+ * four partial sums for some token counts: a program with a varying batch
+ * takes the largest need of the counts it uses.  Returns 0
  * if the arguments are invalid (ee_last_error() says why). */
 size_t ee_workspace_bytes(int n_exits, const ee_exit *exits, int64_t n_tokens);
 

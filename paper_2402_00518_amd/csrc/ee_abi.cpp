@@ -3,6 +3,7 @@
 // backward passes.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdarg>
 #include <cstdint>
@@ -83,7 +84,8 @@ Layout layout(const ee_exit &e, int64_t n) {
     return o;
   };
   const bool normed = e.kind == EE_EXIT_NORM || e.kind == EE_EXIT_MLP;
-  if (normed) L.z = take(N * h * es);
+  const bool mlp = e.kind == EE_EXIT_MLP;
+  if (normed && !mlp) L.z = take(N * h * es);
   L.zht = take(h * ldn * es);
   L.r = take(ldn * 4);
   L.P = take(V * ldn * es);
@@ -103,19 +105,36 @@ Layout layout(const ee_exit &e, int64_t n) {
     L.gsum = take(V * 4);
     L.dbp = take(static_cast<size_t>(L.vtiles) * h * 4);
   }
-  if (e.kind == EE_EXIT_MLP) {
-    L.u = take(N * h * es);
+  if (mlp) {
     L.uhat = take(h * ldn * es);  // U_hat^T, token-contiguous
     L.rx = take(ldn * 4);
     L.hg = take(2 * N * I * es);  // (H_g, H_u) side by side per element
     L.act = take(N * I * es);
-    L.ys = ee::split_tail(f32, static_cast<int>(n), static_cast<int>(h), static_cast<int>(I));
-    L.y = take(static_cast<size_t>(L.ys.splits) * N * h * 4);
-    L.zs = ee::split_tail(f32, static_cast<int>(n), static_cast<int>(h), static_cast<int>(V));
-    L.dz = take(static_cast<size_t>(L.zs.splits) * N * h * 4);
+    const size_t slice = N * h * 4;
+    auto split = [&](size_t K, int most) {
+      return ee::split_tail(f32, static_cast<int>(n), static_cast<int>(h), static_cast<int>(K), most);
+    };
+    if (!f32) {
+      L.ys = split(I, 4);
+      L.zs = split(V, 4);
+    }
+    L.y = take(static_cast<size_t>(L.ys.splits) * slice);
     L.dy = take(N * h * es);
+    L.dz = take(static_cast<size_t>(L.zs.splits) * slice);
     L.dhg = take(I * ldn * es);  // dH_g^T, token-contiguous
     L.dhu = take(I * ldn * es);
+    L.u = take(N * h * es);
+    L.z = take(N * h * es);
+    if (f32) {
+      // Slices 1.. of the split products lie over what follows Y and dZ: nothing
+      // there is live from the product to the pass that adds its slices up
+      // (down projection: U has been read, Z and dY .. dH_u are still to come;
+      // dZ: U and Z have been read, dH_g and dH_u are still to come), and the need
+      // stays what it is without a split, so more tokens never need less.
+      auto most = [&](size_t first) { return static_cast<int>(std::min<size_t>(4, (cur - first) / slice)); };
+      L.ys = split(I, most(L.y));
+      L.zs = split(V, most(L.dz));
+    }
     L.dgpg = take(static_cast<size_t>(L.itiles) * h * 4);
     L.dgpu = take(static_cast<size_t>(L.itiles) * h * 4);
   }

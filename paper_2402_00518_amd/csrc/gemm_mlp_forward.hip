@@ -75,13 +75,13 @@ double launch_span(int64_t full, int64_t parts, int K, int kchunk) {
 
 int split_kchunk(int K, int splits) { return cdiv(cdiv(K, splits), 64) * 64; }
 
-SplitTail split_tail(bool f32, int n, int h, int K) {
+SplitTail split_tail(bool f32, int n, int h, int K, int most) {
   SplitTail best{n, 0, 1};
   if (n <= 0) return best;
   if (f32) {
-    // every output as up to 4 partial sums of at least 256 values of K, as long
-    // as the 64 x 64 tiles leave two blocks a CU unfilled
-    const int s = static_cast<int>(std::min<int64_t>({4, 2 * kCus / (static_cast<int64_t>(cdiv(n, 64)) * cdiv(h, 64)), K / 256}));
+    // every output as up to `most` partial sums of at least 256 values of K, as
+    // long as the 64 x 64 tiles leave two blocks a CU unfilled
+    const int s = static_cast<int>(std::min<int64_t>({most, 2 * kCus / (static_cast<int64_t>(cdiv(n, 64)) * cdiv(h, 64)), K / 256}));
     return s > 1 ? SplitTail{0, 0, cdiv(K, split_kchunk(K, s))} : best;
   }
   // the last few shapes asked for (a layout asks for two per call)

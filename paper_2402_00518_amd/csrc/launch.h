@@ -170,8 +170,9 @@ int split_kchunk(int K, int splits);
 // adds X) in place, slice z at Y + z n h, so Y holds splits n h floats;
 // launch_row_rms_split with the same split adds them up.
 // split_tail: the split for n tokens by h features over a sum of depth K (a
-// shape-only rule that simulates the dispatch of a few candidates).
-SplitTail split_tail(bool f32, int n, int h, int K);
+// shape-only rule that simulates the dispatch of a few candidates; fp32: at
+// most `most` slices, 4 at the most in bf16).
+SplitTail split_tail(bool f32, int n, int h, int K, int most);
 hipError_t gemm_down_residual(bool f32, const void *act, const void *w_down, const void *x, int n,
                               int h, int inter, float *y, hipStream_t stream, SplitTail sp = SplitTail{0, 0, 1});
 // dZ[n][h] = G W_out with G stored transposed [V][ldn]  (fp32 out), with

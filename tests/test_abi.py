@@ -88,6 +88,15 @@ def test_workspace_bytes():
     assert B.lib().ee_workspace_bytes(0, (B.EeExit * 1)(), 10) == 0
 
 
+@pytest.mark.parametrize("h,V,I", [(512, 2000, 1408), (1024, 8000, 2816), (256, 4000, 64), (8192, 500, 64)])
+def test_f32_workspace_serves_fewer_tokens(h, V, I):
+    """A workspace sized for the largest batch is enough for a shorter one (the
+    slices of fp32 split products take no room of their own)."""
+    e = fake_exit(B.EE_EXIT_MLP, h=h, V=V, I=I, dtype=B.EE_F32)
+    need = [B.ee_workspace_bytes([e], n) for n in range(1, 2200)]
+    assert all(a <= b for a, b in zip(need, need[1:]))
+
+
 @pytest.mark.parametrize("field,value,code,needle", [
     ("hidden", 100, B.EE_ERR_SHAPE, "hidden"),
     ("hidden", 0, B.EE_ERR_SHAPE, "hidden"),

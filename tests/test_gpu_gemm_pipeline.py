@@ -49,6 +49,8 @@ SMALL_TILE_CASES = [
     ("f32_small", W.EXIT_NORM, 65, 64, 129, 0, "f32"),
     ("f32_small_mlp", W.EXIT_MLP, 100, 192, 203, 320, "f32"),
     ("f32_split", W.EXIT_MLP, 150, 128, 1100, 576, "f32"),
+    # the slices of dZ limited by the room behind it
+    ("f32_split_narrow", W.EXIT_MLP, 150, 512, 1100, 64, "f32"),
     ("f32_big_logits", W.EXIT_NORM, 100, 64, 32700, 0, "f32"),
     ("f32_big_gate_up", W.EXIT_MLP, 500, 64, 100, 4096, "f32"),
     ("f32_big_dz", W.EXIT_MLP, 4000, 1024, 100, 64, "f32"),

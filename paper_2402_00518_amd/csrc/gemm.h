@@ -25,6 +25,7 @@
 #include <algorithm>
 
 #include "ee_device.h"
+#include "launch.h"
 #include "ring.h"
 
 namespace ee {
@@ -618,11 +619,7 @@ hipError_t launch_gemm_pair(Operand A1, Operand B1, GemmShape s1, const typename
   return hipGetLastError();
 }
 
-// Tile choice.
-// bf16: the 128 x 128 tile where the 256 x 256 tiles fill at most half of the
-// CUs (us, 256 against 128: 80 tiles of K 1024 29 against 20, 64 of K 2048 42
-// against 28, 128 of K 2048 51 against 46, 160 of K 4096 79 against 98).
-inline bool use_mid_tile(int64_t big_tiles) { return big_tiles <= kLoopBlocks / 2; }
+// Tile choice; bf16: gemm_mid_tile.
 // fp32: rounds of tiles on 256 CUs, the 64 x 64 tile costing 0.3 of a 128 x 128
 // one (us, 128 against 64: 16 tiles of K 512 35 against 13, 128 of K 1000 71
 // against 42, 352 of K 2048 239 against 205, 256 of K 512 43 against 49, 1008
@@ -639,7 +636,7 @@ template <class Cfg> int64_t tiles_of(const GemmShape &s) {
 template <typename T, class F, class... S>
 hipError_t with_tile(F &&f, const S &...shapes) {
   if constexpr (std::is_same<T, bf16_t>::value) {
-    if (use_mid_tile((tiles_of<CfgBig>(shapes) + ...))) return f(CfgMid{});
+    if (gemm_mid_tile((tiles_of<CfgBig>(shapes) + ...))) return f(CfgMid{});
     return f(CfgBig{});
   } else {
     if (use_f32_small((tiles_of<CfgF32>(shapes) + ...), (tiles_of<CfgF32Small>(shapes) + ...))) return f(CfgF32Small{});

@@ -5,6 +5,8 @@
 namespace ee {
 
 static_assert(CfgBig::WN == 64 && CfgMid::WN == 64 && CfgF32::WN == 64 && CfgF32Small::WN == 64, "one slice width");
+bool gemm_mid_tile(int64_t big_tiles) { return big_tiles <= kLoopBlocks / 2; }
+
 int gemm_part_cols(bool) { return CfgBig::WN; }
 
 hipError_t gemm_logits(bool f32, const void *w_out, const void *z, int vocab, int n, int h, void *P, int ldn,

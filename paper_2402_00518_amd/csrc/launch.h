@@ -21,6 +21,12 @@ struct SplitTail {
   int splits;  // 1: no split
 };
 
+// Do bf16 products with this many 256 x 256 tiles take 128 x 128 ones?  Where
+// the former fill at most half of the CUs (us, 256 against 128: 80 tiles of K
+// 1024 29 against 20, 64 of K 2048 42 against 28, 128 of K 2048 51 against 46,
+// 160 of K 4096 79 against 98).
+bool gemm_mid_tile(int64_t big_tiles);
+
 // Width of the column slices over which the logits and weight-gradient
 // GEMMs keep their softmax and gain-gradient partials (one wave's columns).
 int gemm_part_cols(bool f32);

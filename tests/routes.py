@@ -13,6 +13,23 @@ def _rule(symbol, *types):
     return f
 
 
+def mid_tile(big_tiles):
+    """Do bf16 products with this many 256 x 256 tiles take 128 x 128 ones?"""
+    return _rule("_ZN2ee13gemm_mid_tileEl", ctypes.c_int64)(big_tiles)
+
+
+class _SplitTail(ctypes.Structure):
+    _fields_ = [("tok0", ctypes.c_int), ("feat0", ctypes.c_int), ("splits", ctypes.c_int)]
+
+
+def split_tail(f32, n, h, k, most=4):
+    """Split of an n x h product over k: (first split token, first split feature, slices)."""
+    f = ctypes.CDLL(B.LIB_PATH)["_ZN2ee10split_tailEbiiii"]
+    f.restype, f.argtypes = _SplitTail, (ctypes.c_bool,) + (ctypes.c_int,) * 4
+    s = f(f32, n, h, k, most)
+    return s.tok0, s.feat0, s.splits
+
+
 _INT3 = (ctypes.c_int,) * 3
 
 

@@ -1,19 +1,21 @@
-"""The bf16 product's pipeline at its edges: one, two and three stages of K,
-K that ends inside a stage (operands read MN-major), operands of a fraction of
-a tile, and a workspace that holds NaN before the step (nothing the products
-multiply may be left over from it).  The bars are those of test_gpu_parity."""
+"""The products' tiles at their edges, every tile of each data type: one, two and
+three stages of K, K that ends inside a stage (operands read MN-major), operands
+of a fraction of a tile, and a workspace that holds NaN before the step (nothing
+the products multiply may be left over from it).  The bars are those of
+test_gpu_parity."""
 
 import pytest
 import torch
 
 import workloads as W
+from routes import mid_tile, split_tail
 from test_gpu_parity import compare_full, gpu, say, small  # noqa: F401 (gpu: the module's GPU fixture)
 
 pytestmark = pytest.mark.gpu
 
 CASES = [
-    # name, kind, N, h, V, I: stages of the logits product h / 64, of dW_out
-    # ceil(N / 64), of dZ ceil(V / 64), of dW_down ceil(N / 64)
+    # bf16, 128 x 128 tiles.  name, kind, N, h, V, I: stages of the logits
+    # product h / 64, of dW_out ceil(N / 64), of dZ ceil(V / 64), of dW_down ceil(N / 64)
     ("pipe_one_stage", W.EXIT_NORM, 5, 64, 65, 0),
     ("pipe_two_stages", W.EXIT_NORM, 65, 128, 257, 0),
     ("pipe_three_stages", W.EXIT_NORM, 129, 192, 1000, 0),
@@ -28,7 +30,56 @@ CASES = [
 def test_pipeline_edges(name, kind, n, h, v, inter):
     from paper_2402_00518_amd.session import Session
     say(f"case: {name} N={n} h={h} V={v} I={inter}")
+    assert all(mid_tile(t) for t in big_tiles(n, h, v, inter).values())
     b = small(kind, n, h, v, inter, seed=9, name=name)
+    s = Session.from_batch(b)
+    s.ws.fill_(0xFF)
+    s.step()
+    torch.cuda.synchronize()
+    s.check_device_error()
+    compare_full(s, b, case=name)
+
+
+def big_tiles(n, h, v, inter):
+    """256 x 256 tiles of each launch of a step (splits not counted)."""
+    def t(a, b):
+        return -(-a // 256) * -(-b // 256)
+    tiles = {"logits": t(n, v), "dW_out": t(h, v)}
+    if inter:
+        tiles.update(gate_up=t(n, 2 * inter), down=t(n, h), dZ=t(-(-n // 64) * 64, h), dA_dW_down=t(n, inter) + t(h, inter),
+                     dW_gate_up=2 * t(h, inter))
+    return tiles
+
+
+BIG_TILE_CASES = [
+    # bf16, 256 x 256 tiles, and the products that take them: one, two and three
+    # stages of K
+    ("big_one_stage", W.EXIT_NORM, 5, 64, 130 * 256 + 1, 0, ("logits", "dW_out")),
+    ("big_two_stages", W.EXIT_NORM, 65, 128, 130 * 256 + 1, 0, ("logits", "dW_out")),
+    ("big_three_stages", W.EXIT_NORM, 129, 192, 130 * 256 + 255, 0, ("logits", "dW_out")),
+    ("big_gate_up", W.EXIT_MLP, 300, 64, 100, 8320, ("gate_up",)),
+    # dZ, both operands MN-major: one stage that ends inside K, two and three;
+    # the down projection of one stage
+    ("big_dz_tail_33", W.EXIT_MLP, 1030, 8192, 33, 64, ("down", "dZ")),
+    ("big_dz_tail_65", W.EXIT_MLP, 1030, 8192, 65, 64, ("down", "dZ")),
+    ("big_dz_tail_129", W.EXIT_MLP, 1030, 8192, 129, 64, ("down", "dZ")),
+    # its tokens past 2048 as four slices, the last one with a ragged end
+    ("big_dz_split", W.EXIT_MLP, 2310, 8192, 1999, 64, ("down", "dZ")),
+    # dW_down over a single stage that ends inside K, beside dA; the gate and up pair
+    ("big_down_one_stage", W.EXIT_MLP, 40, 8192, 65, 1088, ("dA_dW_down", "dW_gate_up")),
+    ("big_down_two_stages", W.EXIT_MLP, 70, 8192, 65, 1088, ("dA_dW_down", "dW_gate_up")),
+]
+
+
+@pytest.mark.parametrize("name,kind,n,h,v,inter,big", BIG_TILE_CASES, ids=[c[0] for c in BIG_TILE_CASES])
+def test_big_tile_edges(name, kind, n, h, v, inter, big):
+    from paper_2402_00518_amd.session import Session
+    say(f"case: {name} N={n} h={h} V={v} I={inter}")
+    tiles = big_tiles(n, h, v, inter)
+    assert not any(mid_tile(tiles[p]) for p in big)
+    if "dZ" in big:
+        assert (split_tail(False, n, h, v)[2] > 1) == ("split" in name)
+    b = small(kind, n, h, v, inter, seed=11, name=name)
     s = Session.from_batch(b)
     s.ws.fill_(0xFF)
     s.step()

@@ -5,6 +5,10 @@
 
 #include "ee_device.h"
 
+// (load_lds16 names m0, which the compiler warns is a register it reserves)
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
+
 namespace ee {
 
 struct Operand {
@@ -25,7 +29,7 @@ __device__ __forceinline__ void load_lds16(const char *base, uint32_t off, uint3
       static_cast<uint64_t>(static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(b >> 32)))) << 32);
   lds = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(lds)));
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(off), "s"(base)
-               : "memory");
+               : "memory", "m0");
 }
 template <int N> __device__ __forceinline__ void wait_vm() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
 __device__ __forceinline__ void wait_lgkm() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
@@ -401,3 +405,5 @@ struct RingF32 {
 };
 
 }  // namespace ee
+
+#pragma clang diagnostic pop

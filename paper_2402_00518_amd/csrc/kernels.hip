@@ -1054,11 +1054,22 @@ hipError_t launch_seed_or_scale(bool f32, void *P, void *x_hat_t, const float *p
   return hipGetLastError();
 }
 
-// 32 rows a block where the seed's 128 give fewer than 448 blocks (2048 tokens
-// and 32003 rows: 251 blocks of 128 rows, one a CU, 40 us, 1001 of 32 29 us),
-// else 128, as each block loads its tokens' coefficients once (4096 tokens and
-// 32000 rows: 500 blocks of 128 59 us, 2000 of 32 63.5 us).
+// 32 rows a block, as the seed's 128 leave too few blocks or a last round of
+// them that is far from full, except where the rows of P lie a multiple of 8 KB
+// apart (many blocks then read the same few memory channels at once) and two
+// or more rounds of 128-row blocks are full.  us a step of an exit of h 512 with
+// 32 rows against 128 (bf16; blocks of 128 rows in brackets):
+//   4096 tokens: V 8000 (126) 145/155, 16000 (250) 221/226, 24000 (376) 298/305,
+//   28000 (438) 332/338, 32000 (500) 370/368; 8192 tokens: 8000 (252) 253/252,
+//   12000 (376) 325/335, 20000 (628) 506/511, 24000 (752) 573/570, 32000 (1000)
+//   730/728.  The kernel alone, rows not a multiple of 8 KB apart: 2048 tokens, V
+//   32000 25/34, 64000 (500) 46/51; 3000 tokens, 32000 (500) 34/44.
 constexpr int kGsumRowsFew = 32;
+int gsum_rows(bool f32, int ldn, int vocab) {
+  const bool camp = static_cast<int64_t>(ldn) * (f32 ? 4 : 2) % 8192 == 0;
+  const int64_t blocks = static_cast<int64_t>(cdiv(vocab, kSeedRows)) * seed_chunks(ldn), rounds = (blocks + 255) / 256;
+  return camp && rounds >= 2 && 100 * blocks >= 95 * 256 * rounds ? kSeedRows : kGsumRowsFew;
+}
 // Row sums of G = diag(coef) P' per 2048-token chunk (the seed's partials),
 // for the bias gradient of an exit in the unshifted form, after the operand
 // scale has shifted P's target entries; nothing if the exit fell back to
@@ -1081,7 +1092,7 @@ hipError_t launch_gsum_unshifted(bool f32, const void *P, const float *coef, int
     EE_DISPATCH(f32, hipLaunchKernelGGL((gsum_unshifted_kernel<T, ROWS>), grid, dim3(256), 0, stream,
                                         static_cast<const T *>(P), coef, n, ldn, vocab, fallback, gsum_part));
   };
-  if (static_cast<int64_t>(cdiv(vocab, kSeedRows)) * seed_chunks(ldn) < 448)
+  if (gsum_rows(f32, ldn, vocab) == kGsumRowsFew)
     go(std::integral_constant<int, kGsumRowsFew>{});
   else
     go(std::integral_constant<int, kSeedRows>{});

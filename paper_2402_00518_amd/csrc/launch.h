@@ -119,6 +119,7 @@ hipError_t launch_seed_or_scale(bool f32, void *P, void *x_hat_t, const float *p
 // set (the seed wrote them), the row sums of G = diag(coef) P' per chunk of
 // 2048 tokens, gsum_part[chunk][v] = sum_{c in chunk, c < n} coef[c] P'[v][c],
 // as launch_seed's.
+int gsum_rows(bool f32, int ldn, int vocab);  // rows of P a block takes
 hipError_t launch_gsum_unshifted(bool f32, const void *P, const float *coef, int n, int ldn, int vocab,
                                  const int *fallback, float *gsum_part, hipStream_t stream);
 

@@ -18,6 +18,13 @@ def mid_tile(big_tiles):
     return _rule("_ZN2ee13gemm_mid_tileEl", ctypes.c_int64)(big_tiles)
 
 
+def gsum_rows(f32, ldn, vocab):
+    """Rows of the logit gradient that a block of the row-sum kernel takes."""
+    f = ctypes.CDLL(B.LIB_PATH)["_ZN2ee9gsum_rowsEbii"]
+    f.restype, f.argtypes = ctypes.c_int, (ctypes.c_bool, ctypes.c_int, ctypes.c_int)
+    return f(f32, ldn, vocab)
+
+
 class _SplitTail(ctypes.Structure):
     _fields_ = [("tok0", ctypes.c_int), ("feat0", ctypes.c_int), ("splits", ctypes.c_int)]
 

@@ -2,7 +2,7 @@
 
 import pytest
 
-from routes import skinny_down, skinny_logits
+from routes import gsum_rows, skinny_down, skinny_logits
 
 # (vocab, tokens, hidden): 32-row blocks measured faster than the ring, and slower
 FEW = [(2000, 1, 512), (2000, 1, 8192), (8192, 32, 4096), (10000, 16, 4096), (16384, 8, 8192), (16384, 24, 4096),
@@ -26,3 +26,10 @@ def test_many_rows_take_the_ring(vocab, n, h):
 def test_down_projection():
     assert skinny_down(512, 1, 1344) and skinny_down(1024, 250, 1024) and skinny_down(2048, 128, 2048)
     assert not skinny_down(2048, 250, 2048) and not skinny_down(5120, 8, 13824) and not skinny_down(2048, 1, 5504)
+
+
+def test_row_sums_of_the_logit_gradient():
+    for n, v in [(2048, 4000), (2048, 64000), (3008, 32000), (4096, 8000), (4096, 16000), (4096, 28000), (8192, 20000)]:
+        assert gsum_rows(False, n, v) == 32
+    for n, v in [(4096, 32000), (8192, 16000), (8192, 24000), (8192, 32000)]:
+        assert gsum_rows(False, n, v) == 128

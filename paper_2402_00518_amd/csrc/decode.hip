@@ -465,7 +465,10 @@ hipError_t launch_ring_cfg(Operand W, int R, Operand Z, int B, int K, int splits
 // 140 -> 111 us, 7B 74 -> 62; h 1024, 2048 and 5120 gain nothing), where the
 // registers allow it.  A narrow product (the down projection) is split over K
 // and takes 64 rows a block (13B MLP at 64 tokens: 248 us unsplit, 189 split,
-// 180 with 64 rows).
+// 180 with 64 rows) as long as 128-row blocks would leave half of the CUs idle
+// (us a call, V 8000 or 32000, 64 rows against 128: h 5120, I 13824, 120 blocks of
+// 128, 64 tokens 180/190; h 8192, I 22016, 128 blocks, 100 tokens 378/396; h 6144,
+// I 16384, 144 blocks, 100 tokens 298/261; h 8192, 192 blocks, 100 tokens 434/395).
 constexpr int kCampBytes = 8192;
 template <class Epi, bool PAIR>
 hipError_t launch_ring(Operand W, int R, Operand Z, int B, int K, int splits, const typename Epi::Params &ep,
@@ -475,7 +478,7 @@ hipError_t launch_ring(Operand W, int R, Operand Z, int B, int K, int splits, co
   const bool camp = W.ld * 2 % kCampBytes == 0 && splits == 1;
   const int64_t blocks = (static_cast<int64_t>(PAIR ? 2 * R : R) + 127) / 128 * ((B + 127) / 128) * splits;
   if constexpr (Epi::kSplit) {
-    if (B <= 128 && blocks < 200) {
+    if (B <= 128 && blocks <= 136) {
       if (B <= 32) return launch_ring_cfg<Epi, 64, 32, 32, 4, 1, PAIR>(W, R, Z, B, K, splits, ep, stream);
       if (B <= 64) return launch_ring_cfg<Epi, 64, 64, 32, 4, 1, PAIR>(W, R, Z, B, K, splits, ep, stream);
       return launch_ring_cfg<Epi, 64, 128, 64, 4, 1, PAIR>(W, R, Z, B, K, splits, ep, stream);
@@ -595,7 +598,10 @@ hipError_t decode_gate_up(bool f32, const void *w_gate, const void *w_up, int ro
 }
 
 // Slices of the down projection's K: enough for two 64-row blocks a CU (two
-// 128-row blocks past 128 tokens), at most `most`, and 512 values of K each.
+// 128-row blocks past 128 tokens), at most `most`, and 512 values of K each.  (One
+// block a CU: h 5120, I 13824, 400 tokens 351 -> 375 us a call, h 4096, I 11008,
+// 500 tokens 272 -> 255; three or four: the same within 1%, h 8192, I 22016, 400
+// tokens 873 -> 915.)
 int decode_residual_splits(bool f32, int rows, int n, int k, int most) {
   if (f32 || decode_skinny_down(rows, n, k)) return 1;
   const int64_t bm = n <= 128 ? 64 : 128, blocks = (rows + bm - 1) / bm * ((n + 127) / 128);

@@ -228,7 +228,12 @@ ee_status ee_check_device_error(void *ws, size_t ws_bytes, void *stream);
  * Errors as for the training entry points (nothing is enqueued); threshold
  * must not be NaN.  Logits are accumulated in fp32 from the exit's dtype;
  * no logit tensor is written (each 32-row slice of W_out is reduced to
- * per-token max / argmax / sum of exponentials on the fly). */
+ * per-token max / argmax / sum of exponentials on the fly).  The order of
+ * the fp32 sums depends on n_rows: the same hidden state decided with another
+ * number of rows in the call may differ in the last bits of its logits (for an
+ * MLP exit also through the rounding to the exit's dtype), so in its
+ * confidence, in its flag next to the threshold and in its token between
+ * almost equal logits.  Equal calls give equal results. */
 size_t ee_decode_workspace_bytes(const ee_exit *e, int64_t n_rows);
 
 ee_status ee_exit_decide(const ee_exit *e, const void *hidden, int64_t n_rows,

@@ -53,9 +53,9 @@ struct TileCfg {
   static constexpr int STAGES = STAGES_;  // LDS stages
   static constexpr int SMEM_BYTES = STAGES * STAGE_BYTES;
 };
-// 256 x 256 tile, 8 waves of 128 x 64 (two waves per SIMD): every bf16 GEMM.
-// 1.5x the MFMA work per byte read from LDS of the small tile, and a second
-// wave per SIMD to issue while the other waits.
+// 256 x 256 tile, 8 waves of 128 x 64 (two waves per SIMD), for bf16 products
+// with enough of them: 1.5x the MFMA work per byte read from LDS of the small
+// tile, and a second wave per SIMD to issue while the other waits.
 using CfgBig = TileCfg<256, 256, 128, 64, 1>;
 // 128 x 128 tile, 64 x 64 per wave, a ring of 2 stages: bf16 products with too
 // few 256 x 256 tiles to fill the chip.
@@ -172,8 +172,9 @@ struct GemmBlock<float, AK, BKM, Epi, Cfg, LOOP> {
 // WR / 2 .. : WR rows a wave (128 for A, 64 for B), WR / 2 of them per half.
 //
 // K-major: a half is 128 LDS rows of 64 values of K (128 bytes), 16-byte
-// chunk c of row r at chunk c ^ ((r / 2) mod 8) (conflict-free, see lds_off).
-// The load writes LDS linearly, so the XOR is applied to the address a lane
+// chunk c of row r at chunk c ^ ((r / 2) mod 8): 16 lanes of a fragment read, served
+// at a time from 256 bytes of banks (two LDS rows), read one chunk of 16
+// consecutive rows, and the XOR puts rows of equal parity on distinct chunks.  The load writes LDS linearly, so the XOR is applied to the address a lane
 // reads from; it stays inside the row's 128-byte line.
 // MN-major: a half is 64 LDS k-rows of 128 operand rows (256 bytes), chunk c of
 // k-row k at c ^ (2 (k mod 4) + 8 (k / 8 mod 2)).  ds_read_b64_tr_b16 gives lane
@@ -546,7 +547,8 @@ template <typename T, bool AK, bool BKM>
 bool gemm_shape_ok(const Operand &A, const Operand &B, const GemmShape &s) {
   constexpr int BK = 8 * Elem<T>::CH;
   if (((AK || BKM) && s.K % BK != 0) || (!AK && s.M % 8 != 0) || (!BKM && s.N % 8 != 0)) return false;
-  // MN-major loaders keep signed 24-bit k-row strides
+  // MN-major loaders multiply by the k-row stride in bytes as an unsigned 24-bit
+  // number: 2^22 fp32 values are 2^24 bytes
   return !((!AK && A.ld >= (int64_t{1} << 22)) || (!BKM && B.ld >= (int64_t{1} << 22)));
 }
 

@@ -1,4 +1,5 @@
-// Host-callable launchers of the exit-head kernels (defined in kernels.hip).
+// Host-callable launchers of the exit-head kernels (kernels.hip, gemm_*.hip,
+// decode.hip, optim.hip).
 // Every launcher enqueues on `stream` and returns the launch status; shapes
 // have been validated by the caller.
 #pragma once
@@ -14,7 +15,7 @@ constexpr int kTokenPad = 64;     // padding of the token dimension
 // projection and dZ): the outputs of tokens >= tok0 and features >= feat0
 // (one of the two is 0) are computed as `splits` partial sums over slices of
 // K, slice z at z * n * h floats from slice 0; the rest take all of K.
-// split_tail(f32, n, h, K) picks one for a shape.
+// split_tail picks one for a shape.
 struct SplitTail {
   int tok0;
   int feat0;

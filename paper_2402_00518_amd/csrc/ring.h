@@ -1,6 +1,6 @@
-// Building blocks of the bf16 products on v_mfma_f32_16x16x32_bf16 whose operands
-// go straight from memory into LDS, and the ring main loop that small tiles
-// and the decode-time products share.
+// Building blocks of the products whose operands go straight from memory into
+// LDS, and their ring main loops: bf16 on v_mfma_f32_16x16x32_bf16, shared by the
+// small tiles and the decode-time products, and fp32 on v_mfma_f32_32x32x2_f32.
 #pragma once
 
 #include "ee_device.h"
@@ -207,12 +207,14 @@ struct RingOperand {
 // WM x WN.  On return acc holds the wave's outputs, every load has landed and
 // every wave has read what it needs (a barrier was passed since).
 //
-// PARTS = 4: K is summed in four consecutive parts, (0 + 1) + (2 + 3), and the
-// tiles take them in different orders (0123, 1032, 2301, 3210).  Rows whose
-// stride is a power of two lie in the same few memory channels at one K, and
-// tiles that walk K in step all wait for those.  Every tile adds the same
-// values in the same order up to swapped summands, so equal rows still give
-// equal sums.
+// PARTS = 4 or 8: K is summed in that many consecutive parts, as a balanced tree,
+// (0 + 1) + (2 + 3) and for 8 that plus (4 + 5) + (6 + 7), and the tiles take them
+// in PARTS different orders: row tile t starts at part o = t / 8 mod PARTS and
+// takes part p ^ o as its p-th, which swaps the two sides of some sums (4
+// parts: 0123, 1032, 2301, 3210).  Rows whose stride is a power of two lie in
+// the same few memory channels at one K, and tiles that walk K in step all
+// wait for those.  Every tile adds the same values in the same order up to
+// swapped summands, so equal rows still give equal sums.
 template <int BM_, int BN_, int WM_, int WN_, int NS_, bool AK, bool BKM, bool A_PAIR, bool B_PAIR, int PARTS = 1>
 struct Ring {
   static constexpr int BM = BM_, BN = BN_, WM = WM_, WN = WN_, NS = NS_;

@@ -33,6 +33,7 @@ namespace ee {
 struct GemmShape {
   int M, N, K;
   int kchunk = 0;  // split-K: blockIdx.z covers K values [z kchunk, (z + 1) kchunk); 0 = all of K
+  int parts = 1;   // fp32, 128 x 128 tiles: K is summed in this many parts (see RingF32)
 };
 
 constexpr int kRowBytes = 128;
@@ -155,7 +156,7 @@ struct GemmBlock<float, AK, BKM, Epi, Cfg, LOOP> {
     const int kbeg = s.kchunk > 0 ? kz * s.kchunk : 0;
     const int K = (s.kchunk > 0 ? min(s.K, kbeg + s.kchunk) : s.K) - kbeg;
     f32x16_t acc[2][2];
-    R::run(A, m0, s.M, B, n0, s.N, kbeg, K, tid, smem, acc);
+    R::run(A, m0, s.M, B, n0, s.N, kbeg, K, s.parts, tid, smem, acc);
     if (Cfg::KW > 1 && wave > 0) {  // the first wave holds the tile
       static_for<EpiBarriers<Epi>::value>([&](auto) EE_ALWAYS_INLINE { __syncthreads(); });
       return;
@@ -488,7 +489,7 @@ __global__ __launch_bounds__(Cfg::BLOCK, Cfg::MIN_BLOCKS) void gemm_gated_kernel
 // a CU starts its next tile's loads right after the epilogue's barrier,
 // without waiting for a new block to be dispatched (measured at 2.6 us
 // between one weight-gradient tile's end and the next one's start on the
-// freed CU).
+// freed CU).  fp32: two blocks a CU, see gemm_f32_loops.
 template <typename T, bool AK, bool BKM, class Epi, class Cfg>
 __global__ __launch_bounds__(Cfg::BLOCK, Cfg::MIN_BLOCKS) void gemm_persistent_kernel(Operand A, Operand B,
                                                                            GemmShape s,
@@ -571,6 +572,13 @@ hipError_t launch_gemm(Operand A, Operand B, GemmShape s, const typename Epi::Pa
       return hipGetLastError();
     }
   }
+  if constexpr (std::is_same<T, float>::value && Cfg::KW == 1) {
+    if (splits == 1 && gemm_f32_loops(blocks)) {
+      hipLaunchKernelGGL((gemm_persistent_kernel<T, AK, BKM, Epi, Cfg>), dim3(2 * kLoopBlocks), dim3(Cfg::BLOCK), 0,
+                         stream, A, B, s, ep);
+      return hipGetLastError();
+    }
+  }
   hipLaunchKernelGGL((gemm_kernel<T, AK, BKM, Epi, Cfg>), dim3(static_cast<unsigned>(blocks), 1, splits),
                      dim3(Cfg::BLOCK), 0, stream, A, B, s, ep);
   return hipGetLastError();
@@ -621,17 +629,15 @@ hipError_t launch_gemm_pair(Operand A1, Operand B1, GemmShape s1, const typename
   return hipGetLastError();
 }
 
-// Tile choice; bf16: gemm_mid_tile.
-// fp32: rounds of tiles on 256 CUs, the 64 x 64 tile costing 0.3 of a 128 x 128
-// one (us, 128 against 64: 16 tiles of K 512 35 against 13, 128 of K 1000 71
-// against 42, 352 of K 2048 239 against 205, 256 of K 512 43 against 49, 1008
-// of K 512 144 against 179).
-inline bool use_f32_small(int64_t tiles, int64_t small_tiles) {
-  const int64_t r = cdiv(tiles, kLoopBlocks), rs = cdiv(small_tiles, kLoopBlocks);
-  return 3 * rs < 10 * r;
-}
+// Tile choice: gemm_mid_tile (bf16) and gemm_f32_small.
 template <class Cfg> int64_t tiles_of(const GemmShape &s) {
   return static_cast<int64_t>(cdiv(s.M, Cfg::BM)) * cdiv(s.N, Cfg::BN) * (s.kchunk > 0 ? cdiv(s.K, s.kchunk) : 1);
+}
+
+inline int depth_of(const GemmShape &s) { return s.kchunk > 0 ? std::min(s.kchunk, s.K) : s.K; }
+
+template <class... S> int parts_of(const S &...shapes) {
+  return gemm_f32_parts((tiles_of<CfgF32>(shapes) + ...), (tiles_of<CfgF32Small>(shapes) + ...));
 }
 
 // f(configuration) for the tiles that these products take together.
@@ -641,19 +647,22 @@ hipError_t with_tile(F &&f, const S &...shapes) {
     if (gemm_mid_tile((tiles_of<CfgBig>(shapes) + ...))) return f(CfgMid{});
     return f(CfgBig{});
   } else {
-    if (use_f32_small((tiles_of<CfgF32>(shapes) + ...), (tiles_of<CfgF32Small>(shapes) + ...))) return f(CfgF32Small{});
+    if (gemm_f32_small((tiles_of<CfgF32>(shapes) + ...), (tiles_of<CfgF32Small>(shapes) + ...), std::max({depth_of(shapes)...})))
+      return f(CfgF32Small{});
     return f(CfgF32{});
   }
 }
 
 template <typename T, bool AK, bool BKM, class Epi>
 hipError_t run_gemm(Operand A, Operand B, GemmShape s, const typename Epi::Params &ep, hipStream_t stream) {
+  s.parts = parts_of(s);
   return with_tile<T>([&](auto c) { return launch_gemm<T, AK, BKM, Epi, decltype(c)>(A, B, s, ep, stream); }, s);
 }
 
 template <typename T, bool AK1, bool BKM1, class Epi1, bool AK2, bool BKM2, class Epi2>
 hipError_t run_gemm_pair(Operand A1, Operand B1, GemmShape s1, const typename Epi1::Params &ep1, Operand A2,
                          Operand B2, GemmShape s2, const typename Epi2::Params &ep2, hipStream_t stream) {
+  s1.parts = s2.parts = parts_of(s1, s2);
   return with_tile<T>(
       [&](auto c) {
         return launch_gemm_pair<T, AK1, BKM1, Epi1, AK2, BKM2, Epi2, decltype(c)>(A1, B1, s1, ep1, A2, B2, s2, ep2,

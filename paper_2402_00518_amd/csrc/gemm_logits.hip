@@ -7,6 +7,28 @@ namespace ee {
 static_assert(CfgBig::WN == 64 && CfgMid::WN == 64 && CfgF32::WN == 64 && CfgF32Small::WN == 64, "one slice width");
 bool gemm_mid_tile(int64_t big_tiles) { return big_tiles <= kLoopBlocks / 2; }
 
+int gemm_f32_parts(int64_t tiles, int64_t small_tiles) {
+  return 3 * cdiv(small_tiles, kLoopBlocks) < 10 * cdiv(tiles, kLoopBlocks) ? 4 : 1;
+}
+bool gemm_f32_small(int64_t tiles, int64_t small_tiles, int K) {
+  constexpr int kPair = 2 * kLoopBlocks;  // blocks of a round, two a CU
+  const int64_t rounds = cdiv(tiles, kLoopBlocks);
+  double big = (rounds / 2) * (10.7 + 0.1165 * K) + (rounds % 2) * (4.5 + 0.068 * K);
+  if (gemm_f32_parts(tiles, small_tiles) > 1) big *= 1.03;  // what the parts cost
+  const double one = 5.3 + 0.0188 * K, two = 6.0 + 0.0313 * K;  // a round of small tiles, one and two a CU
+  const int64_t rest = small_tiles % kPair;
+  double small = static_cast<double>(small_tiles / kPair) * two;
+  if (rest > kLoopBlocks)
+    small += two;
+  else if (rest > 0)  // after a full round, some CUs take two of the rest
+    small += one + (small_tiles > kPair ? 0.7 * (two - one) * static_cast<double>(rest) / kLoopBlocks : 0.0);
+  return small < big;
+}
+bool gemm_f32_loops(int64_t tiles) {
+  const int64_t rest = tiles % (2 * kLoopBlocks);
+  return tiles > 2 * kLoopBlocks && rest > 0 && rest <= kLoopBlocks;
+}
+
 int gemm_part_cols(bool) { return CfgBig::WN; }
 
 hipError_t gemm_logits(bool f32, const void *w_out, const void *z, int vocab, int n, int h, void *P, int ldn,

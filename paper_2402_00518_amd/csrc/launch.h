@@ -27,6 +27,27 @@ struct SplitTail {
 // 1024 29 against 20, 64 of K 2048 42 against 28, 128 of K 2048 51 against 46,
 // 160 of K 4096 79 against 98).
 bool gemm_mid_tile(int64_t big_tiles);
+// Do fp32 products with this many 128 x 128 and 64 x 64 tiles, sums of length K
+// (the longest one of a launch), take the 64 x 64 ones?  By a model of each
+// tile's rounds, us up to a factor, fitted to 1300 launches of 40 to 4096
+// tokens, h 128 to 1024 and V 500 to 16000 timed with both (it takes the slower
+// side by 0.06% in the mean and 16% at worst).  A 64 x 64 tile shares K over four
+// waves, so it wins where K is long and the other tile leaves CUs idle, and
+// loses where its epilogue, on one wave, outweighs a short K (us, 128 against 64:
+// 200 tiles of K 128 15 against 19, 380 of K 128 27/35, 128 of K 1000 71/42, 180 of K
+// 512 39/43, 144 of K 512 38/35, 518 of K 448 92/84, 1008 of K 512 144/179).
+bool gemm_f32_small(int64_t tiles, int64_t small_tiles, int K);
+// Parts of K of an fp32 sum on 128 x 128 tiles: 4, as on a 64 x 64 tile, where the
+// rounds of the two tiles (a small one at 0.3 of the other) come out even or
+// better for the small one, so that precision does not hang on which of two
+// nearly equal tiles a shape takes; else 1, as the parts cost time (see RingF32).
+int gemm_f32_parts(int64_t tiles, int64_t small_tiles);
+// Does a launch of this many 128 x 128 fp32 tiles loop, two blocks a CU?  Two blocks
+// that share a CU end together, and the next two tiles then land there too while
+// other CUs idle; the loop gives every CU its share of a last round of at most
+// one tile a CU (us, a block a tile against the loop: 630 tiles of K 384 100/82, 740
+// of K 384 103/82, 1188 of K 128 61/55; 800 tiles of K 512 139/142).
+bool gemm_f32_loops(int64_t tiles);
 
 // Width of the column slices over which the logits and weight-gradient
 // GEMMs keep their softmax and gain-gradient partials (one wave's columns).

@@ -18,6 +18,25 @@ def mid_tile(big_tiles):
     return _rule("_ZN2ee13gemm_mid_tileEl", ctypes.c_int64)(big_tiles)
 
 
+def f32_small(tiles, small_tiles, k):
+    """Do fp32 products with these counts of 128 x 128 and 64 x 64 tiles take the latter?"""
+    f = ctypes.CDLL(B.LIB_PATH)["_ZN2ee14gemm_f32_smallElli"]
+    f.restype, f.argtypes = ctypes.c_bool, (ctypes.c_int64, ctypes.c_int64, ctypes.c_int)
+    return f(tiles, small_tiles, k)
+
+
+def f32_parts(tiles, small_tiles):
+    """Parts in which 128 x 128 fp32 tiles sum K."""
+    f = ctypes.CDLL(B.LIB_PATH)["_ZN2ee14gemm_f32_partsEll"]
+    f.restype, f.argtypes = ctypes.c_int, (ctypes.c_int64, ctypes.c_int64)
+    return f(tiles, small_tiles)
+
+
+def f32_loops(tiles):
+    """Does a launch of this many 128 x 128 fp32 tiles loop over them?"""
+    return _rule("_ZN2ee14gemm_f32_loopsEl", ctypes.c_int64)(tiles)
+
+
 def gsum_rows(f32, ldn, vocab):
     """Rows of the logit gradient that a block of the row-sum kernel takes."""
     f = ctypes.CDLL(B.LIB_PATH)["_ZN2ee9gsum_rowsEbii"]

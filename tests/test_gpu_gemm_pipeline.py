@@ -8,7 +8,7 @@ import pytest
 import torch
 
 import workloads as W
-from routes import mid_tile, split_tail
+from routes import f32_loops, f32_parts, f32_small, mid_tile, split_tail
 from test_gpu_parity import compare_full, gpu, say, small  # noqa: F401 (gpu: the module's GPU fixture)
 
 pytestmark = pytest.mark.gpu
@@ -105,13 +105,31 @@ SMALL_TILE_CASES = [
     ("f32_big_logits", W.EXIT_NORM, 100, 64, 32700, 0, "f32"),
     ("f32_big_gate_up", W.EXIT_MLP, 500, 64, 100, 4096, "f32"),
     ("f32_big_dz", W.EXIT_MLP, 4000, 1024, 100, 64, "f32"),
+    # 128 x 128 tiles in a loop, all with ragged last tiles: logits and dW_out; with
+    # K in four parts gate and up, and dZ (K tail)
+    ("f32_loop_logits_dw", W.EXIT_NORM, 100, 128, 74001, 0, "f32"),
+    ("f32_loop_parts_gate_up", W.EXIT_MLP, 100, 64, 100, 33088, "f32"),
+    ("f32_loop_parts_dz", W.EXIT_MLP, 4100, 2048, 100, 64, "f32"),
+    # K in four parts without the loop: fewer stages than parts, a ragged last part
+    ("f32_parts_logits", W.EXIT_NORM, 1036, 64, 2862, 0, "f32"),
+    ("f32_parts_dw", W.EXIT_NORM, 300, 384, 7440, 0, "f32"),
 ]
+
+
+def f32_tiles(a, b):
+    return [-(-a // t) * -(-b // t) for t in (128, 64)]
 
 
 @pytest.mark.parametrize("name,kind,n,h,v,inter,dtype", SMALL_TILE_CASES, ids=[c[0] for c in SMALL_TILE_CASES])
 def test_tile_choice_edges(name, kind, n, h, v, inter, dtype):
     from paper_2402_00518_amd.session import Session
     say(f"case: {name} N={n} h={h} V={v} I={inter} {dtype}")
+    products = {"logits": (n, v, h), "dw": (h, v, -(-n // 64) * 64), "gate_up": (n, 2 * inter, h), "dz": (-(-n // 64) * 64, h, v)}
+    for p, (rows, cols, k) in products.items():
+        if name.startswith(("f32_big", "f32_loop", "f32_parts")) and p in name:
+            tiles = f32_tiles(rows, cols)
+            assert not f32_small(*tiles, k) and f32_loops(tiles[0]) == ("loop" in name)
+            assert f32_parts(*tiles) == (4 if "parts" in name else 1)
     b = small(kind, n, h, v, inter, dtype, seed=10, name=name)
     s = Session.from_batch(b)
     s.ws.fill_(0xFF)

@@ -2,7 +2,7 @@
 
 import pytest
 
-from routes import gsum_rows, skinny_down, skinny_logits
+from routes import f32_loops, f32_parts, f32_small, gsum_rows, skinny_down, skinny_logits
 
 # (vocab, tokens, hidden): 32-row blocks measured faster than the ring, and slower
 FEW = [(2000, 1, 512), (2000, 1, 8192), (8192, 32, 4096), (10000, 16, 4096), (16384, 8, 8192), (16384, 24, 4096),
@@ -33,3 +33,25 @@ def test_row_sums_of_the_logit_gradient():
         assert gsum_rows(False, n, v) == 32
     for n, v in [(4096, 32000), (8192, 16000), (8192, 24000), (8192, 32000)]:
         assert gsum_rows(False, n, v) == 128
+
+
+# (128 x 128 tiles, 64 x 64 tiles, K) where the small tiles measured faster, and slower
+@pytest.mark.parametrize("tiles,small,k", [(16, 64, 512), (128, 512, 1000), (144, 517, 512), (260, 1040, 512), (352, 1408, 2048),
+                                           (520, 2072, 2304)])
+def test_f32_small_tiles(tiles, small, k):
+    assert f32_small(tiles, small, k)
+
+
+@pytest.mark.parametrize("tiles,small,k", [(204, 810, 128), (175, 686, 128), (180, 720, 512), (256, 1024, 512), (380, 1520, 128),
+                                           (630, 2375, 128), (671, 2541, 448), (720, 2880, 768), (1008, 4032, 512)])
+def test_f32_large_tiles(tiles, small, k):
+    assert not f32_small(tiles, small, k)
+
+
+def test_f32_parts_where_the_tiles_come_out_even():
+    assert [f32_parts(*t) for t in [(207, 765), (175, 686), (380, 1520), (128, 512)]] == [4] * 4
+    assert [f32_parts(*t) for t in [(256, 1024), (630, 2375), (720, 2880), (1008, 4032)]] == [1] * 4
+
+
+def test_f32_loops():
+    assert [t for t in (256, 512, 513, 768, 769, 1024, 1025, 1280, 1281) if f32_loops(t)] == [513, 768, 1025, 1280]

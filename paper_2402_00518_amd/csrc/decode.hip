@@ -407,11 +407,11 @@ struct DecGateUp {
 // ring.h; blocks of one row tile and several token groups are neighbours on
 // one XCD, so W comes from memory once.  blockIdx.y: split-K slice; blockIdx.z:
 // token groups past the first `groups`.
-template <class Epi, int BM, int BN, int WN, int NS, int Q, bool PAIR>
+template <class Epi, int BM, int BN, int WN, int NS, int Q, bool PAIR, int SEQ>
 __global__ __launch_bounds__(BM / 64 * (BN / WN) * 64) void ring_kernel(Operand W, int R, Operand Z, int B, int K,
                                                                         int kchunk, int groups,
                                                                         typename Epi::Params ep) {
-  using Rg = Ring<BM, BN, 64, WN, NS, true, true, PAIR, false, Q>;
+  using Rg = Ring<BM, BN, 64, WN, NS, true, true, PAIR, false, Q, SEQ>;
   __shared__ __attribute__((aligned(16))) char smem[NS * Rg::STAGE_BYTES];
   const int xcd = blockIdx.x & 7, idx = blockIdx.x >> 3;
   const int tile = (idx / groups) * 8 + xcd, rows = PAIR ? 2 * R : R;
@@ -438,13 +438,13 @@ __global__ __launch_bounds__(BM / 64 * (BN / WN) * 64) void ring_kernel(Operand 
   });
 }
 
-template <class Epi, int BM, int BN, int WN, int NS, int Q, bool PAIR>
+template <class Epi, int BM, int BN, int WN, int NS, int Q, bool PAIR, int SEQ = 1>
 hipError_t launch_ring_cfg(Operand W, int R, Operand Z, int B, int K, int splits, const typename Epi::Params &ep,
                            hipStream_t stream) {
   const int rows = PAIR ? 2 * R : R;
   const int tiles = (rows + BM - 1) / BM, all = (B + BN - 1) / BN, groups = std::min(all, 64);
   const int kchunk = ((K / 64 + splits - 1) / splits) * 64;
-  hipLaunchKernelGGL((ring_kernel<Epi, BM, BN, WN, NS, Q, PAIR>),
+  hipLaunchKernelGGL((ring_kernel<Epi, BM, BN, WN, NS, Q, PAIR, SEQ>),
                      dim3(static_cast<unsigned>((tiles + 7) / 8 * 8 * groups), static_cast<unsigned>(splits),
                           static_cast<unsigned>((all + groups - 1) / groups)),
                      dim3(BM / 64 * (BN / WN) * 64), 0, stream, W, R, Z, B, K, kchunk, groups, ep);
@@ -472,7 +472,7 @@ hipError_t launch_ring_cfg(Operand W, int R, Operand Z, int B, int K, int splits
 constexpr int kCampBytes = 8192;
 template <class Epi, bool PAIR>
 hipError_t launch_ring(Operand W, int R, Operand Z, int B, int K, int splits, const typename Epi::Params &ep,
-                       hipStream_t stream) {
+                       hipStream_t stream, bool exact = false) {
   if (R <= 0 || B <= 0) return hipSuccess;
   if (K % 64 != 0) return hipErrorInvalidValue;
   const bool camp = W.ld * 2 % kCampBytes == 0 && splits == 1;
@@ -482,6 +482,18 @@ hipError_t launch_ring(Operand W, int R, Operand Z, int B, int K, int splits, co
       if (B <= 32) return launch_ring_cfg<Epi, 64, 32, 32, 4, 1, PAIR>(W, R, Z, B, K, splits, ep, stream);
       if (B <= 64) return launch_ring_cfg<Epi, 64, 64, 32, 4, 1, PAIR>(W, R, Z, B, K, splits, ep, stream);
       return launch_ring_cfg<Epi, 64, 128, 64, 4, 1, PAIR>(W, R, Z, B, K, splits, ep, stream);
+    }
+  }
+  if constexpr (std::is_same<Epi, DecLogits>::value) {
+    // Sums as short as the parts of camping rows give, so that the error against
+    // 64 bits is that of K shared by skinny_kernel's waves (confidences: h 5120, V
+    // 20000, 128 tokens 8.3e-7 in one sum, 2.1e-7 in parts and in skinny_kernel; h
+    // 2048, V 32000, 400 tokens 5.2e-7, 2.0e-7, 1.8e-7), for up to 8% more time.
+    if (exact && K > 512 && !(camp && (B <= 64 || blocks <= 256))) {
+      if (B <= 32) return launch_ring_cfg<Epi, 128, 32, 32, 4, 1, PAIR, 8>(W, R, Z, B, K, splits, ep, stream);
+      if (B <= 64) return launch_ring_cfg<Epi, 128, 64, 32, 3, 1, PAIR, 8>(W, R, Z, B, K, splits, ep, stream);
+      if (blocks > 256) return launch_ring_cfg<Epi, 128, 128, 64, 2, 1, PAIR, 8>(W, R, Z, B, K, splits, ep, stream);
+      return launch_ring_cfg<Epi, 128, 128, 64, 4, 1, PAIR, 8>(W, R, Z, B, K, splits, ep, stream);
     }
   }
   if (B <= 32) {
@@ -622,11 +634,11 @@ hipError_t decode_residual(bool f32, const void *w, int rows, const void *z, int
 }
 
 hipError_t decode_logits(bool f32, const void *w_out, int vocab, const void *z, int n, int h, float *part_m,
-                         float *part_l, int32_t *part_arg, hipStream_t stream) {
+                         float *part_l, int32_t *part_arg, hipStream_t stream, bool exact) {
   const DecLogits::Params ep{part_m, part_l, part_arg, n};
   if (f32 || decode_skinny_logits(vocab, n, h))
     EE_DISPATCH(f32, return (launch_skinny<T, DecLogits>(w_out, h, vocab, z, h, n, h, ep, stream)));
-  return launch_ring<DecLogits, false>(Operand{w_out, h}, vocab, Operand{z, h}, n, h, 1, ep, stream);
+  return launch_ring<DecLogits, false>(Operand{w_out, h}, vocab, Operand{z, h}, n, h, 1, ep, stream, exact);
 }
 
 hipError_t decode_decide(const float *part_m, const float *part_l, const int32_t *part_arg, int tiles, int n,

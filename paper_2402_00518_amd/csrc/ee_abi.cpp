@@ -631,7 +631,7 @@ ee_status run_decide(const ee_exit &e, const void *x, int64_t n64, float thresho
   }
   int32_t *pa = reinterpret_cast<int32_t *>(at(ws, L.pa));
   EE_LAUNCH("decode logits partials", s,
-            ee::decode_logits(f32, e.w_out, V, z, n, h, atf(ws, L.pm), atf(ws, L.pl), pa, s));
+            ee::decode_logits(f32, e.w_out, V, z, n, h, atf(ws, L.pm), atf(ws, L.pl), pa, s, e.kind == EE_EXIT_EMBEDDING));
   EE_LAUNCH("decode decision", s,
             ee::decode_decide(atf(ws, L.pm), atf(ws, L.pl), pa, L.tiles, n, threshold, token, confidence, exit_flag,
                               s));

@@ -260,8 +260,10 @@ int decode_residual_splits(bool f32, int rows, int n, int k, int most);
 hipError_t decode_residual(bool f32, const void *w, int rows, const void *z, int n, int k, const void *x,
                            float *y, int splits, float *extra, hipStream_t stream);
 // Softmax partials of S = Z W_out^T: [decode_tiles(vocab)][n] max, sum exp, lowest argmax.
+// exact: Z holds the values that the logits are defined on (not a rounding of
+// them), so the fp32 sums are all of the error and are kept short.
 hipError_t decode_logits(bool f32, const void *w_out, int vocab, const void *z, int n, int h, float *part_m,
-                         float *part_l, int32_t *part_arg, hipStream_t stream);
+                         float *part_l, int32_t *part_arg, hipStream_t stream, bool exact);
 // Greedy token, its probability, and confidence > threshold, per token row.
 hipError_t decode_decide(const float *part_m, const float *part_l, const int32_t *part_arg, int tiles, int n,
                          float threshold, int32_t *token, float *confidence, int32_t *exit_flag,

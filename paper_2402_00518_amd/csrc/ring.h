@@ -215,7 +215,11 @@ struct RingOperand {
 // the same few memory channels at one K, and tiles that walk K in step all
 // wait for those.  Every tile adds the same values in the same order up to
 // swapped summands, so equal rows still give equal sums.
-template <int BM_, int BN_, int WM_, int WN_, int NS_, bool AK, bool BKM, bool A_PAIR, bool B_PAIR, int PARTS = 1>
+//
+// SEQ > 1 (PARTS = 1): K is summed in up to that many consecutive parts, added up
+// in order, for shorter chains of fp32 sums with half of the registers of 4 parts.
+template <int BM_, int BN_, int WM_, int WN_, int NS_, bool AK, bool BKM, bool A_PAIR, bool B_PAIR, int PARTS = 1,
+          int SEQ = 1>
 struct Ring {
   static constexpr int BM = BM_, BN = BN_, WM = WM_, WN = WN_, NS = NS_;
   static constexpr int WAVES_M = BM / WM, WAVES_N = BN / WN, THREADS = WAVES_M * WAVES_N * 64;
@@ -225,6 +229,7 @@ struct Ring {
   static constexpr int LOADS = TA::LOADS + TB::LOADS;
   using Acc = f32x4_t[WM / 16][WN / 16];
   static_assert((NS - 2) * LOADS <= 63, "loads in flight past the waited-for stage");
+  static_assert(PARTS == 1 || SEQ == 1, "one way to take K in parts");
   static_assert(PARTS == 1 || ((PARTS == 4 || PARTS == 8) && AK), "parts: 1, or 4 or 8 of a K-major product");
 
   template <class F> __device__ __forceinline__ static void each(F &&f) {
@@ -300,7 +305,21 @@ struct Ring {
       constexpr int P = decltype(p_)::value;
       each([&](auto i, auto j) EE_ALWAYS_INLINE { acc[i][j] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f}; });
       const int p = P ^ order, len = part_begin(p + 1) - part_begin(p);
-      for (int t = 0; t < len; ++t) consume();
+      if constexpr (SEQ > 1) {
+        const int slen = max((nk + SEQ - 1) / SEQ, 8);  // (512 values of K at least)
+        Acc done;  // the parts before
+        for (int t0 = 0; t0 < nk; t0 += slen) {
+          const int t1 = min(t0 + slen, nk);
+          for (int t = t0; t < t1; ++t) consume();
+          each([&](auto i, auto j) EE_ALWAYS_INLINE {
+            if (t0 > 0) acc[i][j] += done[i][j];
+            done[i][j] = acc[i][j];
+            if (t1 < nk) acc[i][j] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+          });
+        }
+      } else {
+        for (int t = 0; t < len; ++t) consume();
+      }
       if constexpr (PARTS > 1) {
         constexpr int FULL = P == PARTS - 1 ? LEVELS : __builtin_ctz(~P);  // groups that end with this part
         each([&](auto i, auto j) EE_ALWAYS_INLINE {

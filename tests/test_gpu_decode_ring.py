@@ -102,3 +102,19 @@ def test_equal_rows_of_different_tiles_tie(rows, h, v):
     tied = s[:, 140] == s.max(axis=1)
     assert tied.any()
     assert (token[tied] == 140).all()
+
+
+@pytest.mark.parametrize("rows,h,v", [(32, 3072, 17000), (64, 3072, 9000), (100, 3072, 9000), (300, 3072, 17000)])
+def test_embedding_sums_are_short(rows, h, v):
+    """An Embedding exit's logits are products of its inputs as they are, so the
+    order of the fp32 sums is all of the confidences' error: K is taken in at most 8
+    parts of 512 values or more.  One chain over h 3072 gives 1.8e-6 to 3.3e-6 here,
+    parts 2.4e-7 to 4.5e-7 (relative, 2-norm): the bar is twice that."""
+    assert not skinny_logits(v, rows, h)
+    w, b = make_case(W.EXIT_EMBEDDING, rows, h, v, 0, "bf16", seed=34)
+    say(f"case: decode embedding sums rows={rows} h={h} V={v}")
+    _, conf, _ = run_decide(b, 0.5)
+    ref = D.exit_decide(O.exits_from_batch(b)[0], W.decode(b.hidden[0]), 0.5)["confidence"]
+    err = np.linalg.norm(conf - ref) / np.linalg.norm(ref)
+    say(f"  relative error {err:.2e}")
+    assert err <= 9e-7
